@@ -109,77 +109,60 @@ struct TileMap {
   __device__ static int by(int w) { return (w / BX) * 8; }
 };
 
-// Shared staging state of one batch.
+// Shared staging state of one backward batch of at most MAXB list positions.
+template <int MAXB>
 struct BatchLDS {
-  Staged rec[kBlock];
-  uint8_t list[kWaves][kBlock];  // per wavefront: staged slots in list order
+  Staged rec[MAXB];
+  uint8_t list[kWaves][MAXB];     // per wavefront: staged slots in list order
   uint32_t wcnt[kWaves][kWaves];  // [block][staging wave] hits
 };
 
 // Stages pairs [b0, b0 + nb) of the tile list and builds the four per-block
-// lists.  Returns (through cnt) the list length of this thread's wavefront.
-template <int TW>
-__device__ __forceinline__ uint32_t stage_batch(BatchLDS& L, const Rec* __restrict__ rec,
+// lists; returns the list length of this thread's wavefront.  Up to 128 pairs
+// the two halves of the workgroup take the same pairs and two blocks each (the
+// ellipse tests are most of the work), beyond every thread takes one pair and
+// all four blocks.
+template <int TW, int MAXB>
+__device__ __forceinline__ uint32_t stage_batch(BatchLDS<MAXB>& L, const Rec* __restrict__ rec,
                                                 const uint32_t* __restrict__ pval, uint32_t b0, uint32_t nb,
                                                 float ox, float oy) {
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  constexpr int kShare = kBlock / MAXB;        // threads per pair
+  constexpr int kTests = kWaves / kShare;      // blocks per thread
+  constexpr int kStageWaves = kWaves / kShare; // wavefronts over the pairs
+  const int t = threadIdx.x & (MAXB - 1), lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int w0 = (int)__builtin_amdgcn_readfirstlane(wv / kStageWaves) * kTests;  // first block
+  const int sw = wv % kStageWaves;
   uint32_t mask = 0;
   if ((uint32_t)t < nb) {
     const uint32_t e = pval[b0 + t];
     const Rec r = rec[e];
-    L.rec[t] = stage(r, e);
+    if (w0 == 0) L.rec[t] = stage(r, e);
 #pragma unroll
-    for (int w = 0; w < kWaves; w++)
-      if (ellipse_hits(r, ox + TileMap<TW>::bx(w), oy + TileMap<TW>::by(w))) mask |= 1u << w;
+    for (int w = 0; w < kTests; w++)
+      if (ellipse_hits(r, ox + TileMap<TW>::bx(w0 + w), oy + TileMap<TW>::by(w0 + w))) mask |= 1u << w;
   }
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  uint32_t rank[kWaves];
+  uint32_t rank[kTests];
 #pragma unroll
-  for (int w = 0; w < kWaves; w++) {
+  for (int w = 0; w < kTests; w++) {
     const uint64_t bal = __ballot((mask >> w) & 1u);
     rank[w] = __popcll(bal & lt);
-    if (lane == 0) L.wcnt[w][wv] = __popcll(bal);
+    if (lane == 0) L.wcnt[w0 + w][sw] = __popcll(bal);
   }
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kWaves; w++) {
+  for (int w = 0; w < kTests; w++) {
     if ((mask >> w) & 1u) {
       uint32_t off = rank[w];
-      for (int s = 0; s < wv; s++) off += L.wcnt[w][s];
-      L.list[w][off] = (uint8_t)t;
+      for (int s = 0; s < sw; s++) off += L.wcnt[w0 + w][s];
+      L.list[w0 + w][off] = (uint8_t)t;
     }
   }
   uint32_t cnt = 0;
 #pragma unroll
-  for (int s = 0; s < kWaves; s++) cnt += L.wcnt[wv][s];
+  for (int s = 0; s < kStageWaves; s++) cnt += L.wcnt[wv][s];
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(cnt);  // uniform over the wavefront
-}
-
-// The staged records of four consecutive list slots of a wavefront, as the
-// per-pixel loops read them.  The wavefront's list (at most 256 one-byte
-// slots) is held one 32-bit word per lane, so a group's slots come from a
-// readlane instead of an LDS round trip.
-struct Group4 {
-  uint32_t j[4];  // staged slots
-  float4 a[4];    // u, v, cA, cB
-  float2 b[4];    // cC, log2(alpha_cond)
-  float3 c[4];    // r, g, b
-};
-
-// Slots past the list's length wn take the group's first slot instead: the
-// bytes there are left over from earlier use of the LDS, and a record never
-// staged may hold infinities or NaNs, which a zero weight does not cancel.
-__device__ __forceinline__ void fetch_group(const BatchLDS& L, uint32_t lw, uint32_t g, uint32_t wn, Group4& G) {
-  const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)lw, (int)g);
-#pragma unroll
-  for (int u = 0; u < 4; u++) {
-    const uint32_t j = (4 * g + u < wn ? w >> (8 * u) : w) & 255u;
-    G.j[u] = j;
-    G.a[u] = L.rec[j].a;
-    G.b[u] = make_float2(L.rec[j].b.x, L.rec[j].b.y);
-    G.c[u] = make_float3(L.rec[j].c.x, L.rec[j].c.y, L.rec[j].c.z);
-  }
 }
 
 // Forward staging: every wavefront walks the tile's list on its own, 64 list
@@ -411,20 +394,112 @@ __global__ void __launch_bounds__(kBlock, 5) k_blend_fwd(ViewTable vt, DevSettin
   }
 }
 
-// ------------------------------------------------------------- reductions
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_move(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xF, false));
+// ------------------------------------------------------------ backward walk
+// One wavefront, one 8x8 block: the reverse walk takes the block's list in
+// groups of 16 Gaussians, each of the wavefront's four rows of 16 lanes holding
+// the group (lane j: Gaussian j), and steps through the block's pixels four at a
+// time: step `it` takes pixel 16 row + it in every row.  So the Gaussians'
+// gradient sums are per-lane registers added up over the steps (nothing is
+// reduced across lanes per Gaussian), and the two quantities that do chain
+// along the list -- the transmittance and the colour behind -- are scans over
+// the 16 lanes of a row.  A pixel's state lives in lane 16 row + it; a step
+// reads it with row_newbcast as the operand of the instruction that needs it.
+//
+// The chained parts are inline assembly: there a scan step is one instruction
+// in place (a lane without a source keeps its value), which the compiler's
+// lane-move builtins do not reach.  gfx950's DPP reads need two wait states
+// after the VALU write of the register they read.  The compiler provides them
+// for its own instructions, not across these statements: each begins and ends
+// with the wait, and four steps are interleaved, so that a result is read four
+// instructions after it is written.
+typedef float F4v __attribute__((ext_vector_type(4)));
+
+template <int IT>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t x) {  // lane IT of each row
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + IT, 0xF, 0xF, true);
 }
 
-// Sum over the 16 lanes of each row; every lane of the row gets the row total.
-__device__ __forceinline__ float row_sum(float v) {
-  v += dpp_move<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]
-  v += dpp_move<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
-  v += dpp_move<0x124, 0xF>(v);  // row_ror:4
-  v += dpp_move<0x128, 0xF>(v);  // row_ror:8
-  return v;
+// One instruction for each of four steps: operands a b c d of the four, and
+// the lane operation.
+#define SIXDGS_DPP4(op, a0, b0, a1, b1, a2, b2, a3, b3, lanes)       \
+  op " " a0 ", " b0 " " lanes "\n\t" op " " a1 ", " b1 " " lanes     \
+     "\n\t" op " " a2 ", " b2 " " lanes "\n\t" op " " a3 ", " b3 " " \
+     lanes "\n\t"
+#define SIXDGS_ALL " row_mask:0xf bank_mask:0xf"
+#define SIXDGS_SCAN(op, n) \
+  SIXDGS_DPP4(op, "%0", "%0, %0", "%1", "%1, %1", "%2", "%2, %2", "%3", "%3, %3", "row_shl:" n SIXDGS_ALL)
+
+// Steps 4K .. 4K + 3: x[j] = 1 / (1 - alpha) becomes the transmittance in
+// front of each lane's Gaussian, T(pixel 4K + j) times the product of x[j]
+// over the lanes from this one on, and T(pixel) the row's first of these.
+template <int K>
+__device__ __forceinline__ void transmittances(float& T, float (&x)[4]) {
+  constexpr uint64_t kOne = 0x0001000100010001ull << (4 * K);
+  asm("s_nop 1\n\t" SIXDGS_SCAN("v_mul_f32_dpp", "1") SIXDGS_SCAN("v_mul_f32_dpp", "2")
+          SIXDGS_SCAN("v_mul_f32_dpp", "4") SIXDGS_SCAN("v_mul_f32_dpp", "8")
+      "v_mul_f32_dpp %0, %4, %0 row_newbcast:%c9" SIXDGS_ALL "\n\t"
+      "v_mul_f32_dpp %1, %4, %1 row_newbcast:%c10" SIXDGS_ALL "\n\t"
+      "v_mul_f32_dpp %2, %4, %2 row_newbcast:%c11" SIXDGS_ALL "\n\t"
+      "v_mul_f32_dpp %3, %4, %3 row_newbcast:%c12" SIXDGS_ALL "\n\t"
+      "s_mov_b64 vcc, %5\n\t"
+      "v_cndmask_b32_dpp %4, %0, %4, vcc row_newbcast:0" SIXDGS_ALL "\n\t"
+      "s_mov_b64 vcc, %6\n\t"
+      "v_cndmask_b32_dpp %4, %1, %4, vcc row_newbcast:0" SIXDGS_ALL "\n\t"
+      "s_mov_b64 vcc, %7\n\t"
+      "v_cndmask_b32_dpp %4, %2, %4, vcc row_newbcast:0" SIXDGS_ALL "\n\t"
+      "s_mov_b64 vcc, %8\n\t"
+      "v_cndmask_b32_dpp %4, %3, %4, vcc row_newbcast:0" SIXDGS_ALL "\n\t"
+      "s_nop 1"
+      : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(T)
+      : "s"(~kOne), "s"(~(kOne << 1)), "s"(~(kOne << 2)), "s"(~(kOne << 3)), "i"(4 * K), "i"(4 * K + 1),
+        "i"(4 * K + 2), "i"(4 * K + 3)
+      : "vcc");
 }
+
+// Steps 4K .. 4K + 3: q[j] = dL/dC . c times the weight becomes
+// q[j] + f[j] (D(pixel 4K + j) + the sum of q[j] over the lanes past this one),
+// and D(pixel) grows by the row's sum of q[j].  one[j] is 1 in the lanes
+// 4 i + j and 0 in the others; the bank mask keeps to the four lanes 4K ...
+template <int K>
+__device__ __forceinline__ void behind_terms(float& D, float (&q)[4], const float (&f)[4], const float (&one)[4]) {
+  float s0, s1, s2, s3;
+  asm("s_nop 1\n\t"
+      SIXDGS_DPP4("v_add_f32_dpp", "%0", "%4, %4", "%1", "%5, %5", "%2", "%6, %6", "%3", "%7, %7",
+                  "row_shl:1" SIXDGS_ALL " bound_ctrl:1")
+      SIXDGS_SCAN("v_add_f32_dpp", "2") SIXDGS_SCAN("v_add_f32_dpp", "4") SIXDGS_SCAN("v_add_f32_dpp", "8")
+      SIXDGS_DPP4("v_fmac_f32_dpp", "%4", "%0, %9", "%5", "%1, %10", "%6", "%2, %11", "%7", "%3, %12",
+                  "row_shl:1" SIXDGS_ALL " bound_ctrl:1")
+      "v_fmac_f32_dpp %4, %8, %9 row_newbcast:%c17" SIXDGS_ALL "\n\t"
+      "v_fmac_f32_dpp %5, %8, %10 row_newbcast:%c18" SIXDGS_ALL "\n\t"
+      "v_fmac_f32_dpp %6, %8, %11 row_newbcast:%c19" SIXDGS_ALL "\n\t"
+      "v_fmac_f32_dpp %7, %8, %12 row_newbcast:%c20" SIXDGS_ALL "\n\t"
+      "v_fmac_f32_dpp %8, %0, %13 row_newbcast:0 row_mask:0xf bank_mask:%c21\n\t"
+      "v_fmac_f32_dpp %8, %1, %14 row_newbcast:0 row_mask:0xf bank_mask:%c21\n\t"
+      "v_fmac_f32_dpp %8, %2, %15 row_newbcast:0 row_mask:0xf bank_mask:%c21\n\t"
+      "v_fmac_f32_dpp %8, %3, %16 row_newbcast:0 row_mask:0xf bank_mask:%c21\n\t"
+      "s_nop 1"
+      : "=&v"(s0), "=&v"(s1), "=&v"(s2), "=&v"(s3), "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(D)
+      : "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "v"(one[0]), "v"(one[1]), "v"(one[2]), "v"(one[3]), "i"(4 * K),
+        "i"(4 * K + 1), "i"(4 * K + 2), "i"(4 * K + 3), "i"(1 << K));
+}
+
+// Steps 4K .. 4K + 3: sum[c] += dL/dC_c(pixel 4K + j) w[j].
+template <int K>
+__device__ __forceinline__ void colour_terms(float (&sum)[3], const float (&dC)[3], const float (&w)[4]) {
+#pragma unroll
+  for (int c = 0; c < 3; c++)
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %1, %2 row_newbcast:%c6" SIXDGS_ALL "\n\t"
+        "v_fmac_f32_dpp %0, %1, %3 row_newbcast:%c7" SIXDGS_ALL "\n\t"
+        "v_fmac_f32_dpp %0, %1, %4 row_newbcast:%c8" SIXDGS_ALL "\n\t"
+        "v_fmac_f32_dpp %0, %1, %5 row_newbcast:%c9" SIXDGS_ALL
+        : "+v"(sum[c])
+        : "v"(dC[c]), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "i"(4 * K), "i"(4 * K + 1), "i"(4 * K + 2),
+          "i"(4 * K + 3));
+}
+#undef SIXDGS_SCAN
+#undef SIXDGS_ALL
+#undef SIXDGS_DPP4
 
 // a + b after swapping the upper half of a with the lower half of b: lanes
 // 0-31 get a[i] + a[i+32], lanes 32-63 get b[i-32] + b[i].
@@ -440,55 +515,115 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
   return __int_as_float(r[0]) + __int_as_float(r[1]);
 }
 
-// Sums the nine per-lane values of two Gaussians (slots ja and jb) over the
-// wavefront by halving exchanges -- each exchange step halves two values at
-// once -- then adds the totals into LDS columns ja and jb of s_g ([9][kBlock]).
-// After the two swap stages and the row sums, the rows of k0..k4 hold
-// (a0 a2 a1 a3), (a4 a6 a5 a7), (a8 b0 b8 b1), (b2 b4 b3 b5) and (b6 b6 b7 b7).
-__device__ __forceinline__ void wave_sum18_to_lds(const float (&a)[kG2D], const float (&b)[kG2D],
-                                                  float (*s_g)[kBlock], int ja, int jb, int lane) {
-  const float h0 = swap32_add(a[0], a[1]);
-  const float h1 = swap32_add(a[2], a[3]);
-  const float h2 = swap32_add(a[4], a[5]);
-  const float h3 = swap32_add(a[6], a[7]);
-  const float h4 = swap32_add(a[8], b[8]);
-  const float h5 = swap32_add(b[0], b[1]);
-  const float h6 = swap32_add(b[2], b[3]);
-  const float h7 = swap32_add(b[4], b[5]);
-  const float h8 = swap32_add(b[6], b[7]);
-  float k0 = row_sum(swap16_add(h0, h1));
-  float k1 = row_sum(swap16_add(h2, h3));
-  float k2 = row_sum(swap16_add(h4, h5));
-  float k3 = row_sum(swap16_add(h6, h7));
-  float k4 = row_sum(swap16_add(h8, h8));
-  // the row sums complete on every lane here: left to itself the compiler
-  // moves each last add into the branch below, which then needs the rotated
-  // value copied out first (three instructions per sum instead of one)
-  asm volatile("" : "+v"(k0), "+v"(k1), "+v"(k2), "+v"(k3), "+v"(k4));
-  if ((lane & 15) == 0) {
-    const int row = lane >> 4;
-    const int f0 = (row == 0) ? 0 : (row == 1) ? 2 : (row == 2) ? 1 : 3;
-    atomicAdd(&s_g[f0][ja], k0);
-    atomicAdd(&s_g[f0 + 4][ja], k1);
-    const int f2 = (row == 1) ? 0 : (row == 3) ? 1 : 8;
-    atomicAdd(&s_g[f2][row == 0 ? ja : jb], k2);
-    atomicAdd(&s_g[f0 + 2][jb], k3);
-    if ((row & 1) == 0) atomicAdd(&s_g[6 + (row >> 1)][jb], k4);
+// The walk's state: pixel state by lane, and the constant operands of the
+// matrix products.
+struct BwdWave {
+  float T, D;           // transmittance in front of / dL/dC . colour behind the last group taken (lane = pixel)
+  uint32_t lastcmp;     // list positions from here on are not taken (lane = pixel)
+  float dC[3];          // dL/dC (lane = pixel)
+  float dcA[4];         // dL/dC as the pixel operand of dL/dC . c
+  float one[4];         // 1 in the lanes 4 i + j
+};
+
+// A group's Gaussian in this lane, and its sums over the pixels of the row.
+struct BwdGauss {
+  float cA;
+  float dx[8];                // pixel columns
+  float bdy[2], cdy[2];       // the exponent's terms of the row's two pixel lines
+  uint32_t pos;               // list position
+  float s0[2], s1[2], s2[2];  // per pixel line: sums of w, w dx, w dx^2 (w = dL/d(exponent))
+  float col[3];               // colour gradient
+};
+
+// How a group is walked: all pixels take every Gaussian that reaches 1/255
+// (kFree), pixels may stop inside the group (kStops, by lastcmp), or also
+// alpha's clamp may act (kExact).
+enum BwdForm { kFree, kStops, kExact };
+
+// Steps 4K .. 4K + 3 of a group.  col: the Gaussian's colour channel `row` (the
+// fourth is 0), the operand of dL/dC . c.
+template <int K, BwdForm FORM>
+__device__ __forceinline__ void bwd_steps(BwdWave& W, BwdGauss& G, float col) {
+  constexpr int h = K >> 1;
+  const F4v zero = {0.f, 0.f, 0.f, 0.f};
+  const F4v dc = __builtin_amdgcn_mfma_f32_16x16x4f32(W.dcA[K], col, zero, 0, 0, 0);
+  float a[4], f[4], x[4], e[4];
+#pragma unroll
+  for (int j = 0; j < 4; j++) {
+    const float dx = G.dx[(4 * K + j) & 7];
+    // the operations and roundings of log2_alpha
+    const float p = __fmaf_rn(__fmaf_rn(G.cA, dx, G.bdy[h]), dx, G.cdy[h]);
+    bool take = p >= kLog2AlphaMin;
+    e[j] = exp2_fast(p);
+    if constexpr (FORM != kFree) {
+      const uint32_t lc = j == 0   ? row_bcast<4 * K>(W.lastcmp)
+                          : j == 1 ? row_bcast<4 * K + 1>(W.lastcmp)
+                          : j == 2 ? row_bcast<4 * K + 2>(W.lastcmp)
+                                   : row_bcast<4 * K + 3>(W.lastcmp);
+      take = take && G.pos < lc;
+    }
+    a[j] = take ? e[j] : 0.f;
+    if constexpr (FORM == kExact) a[j] = fminf(kAlphaMax, a[j]);
+    x[j] = rcp_fast(1.0f - a[j]);
+    f[j] = -a[j] * x[j];
   }
+  // (f is formed here: the products below take x's registers)
+  asm("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+  transmittances<K>(W.T, x);
+  float wgt[4], q[4];
+#pragma unroll
+  for (int j = 0; j < 4; j++) {
+    wgt[j] = a[j] * x[j];
+    q[j] = dc[j] * wgt[j];
+  }
+  colour_terms<K>(G.col, W.dC, wgt);
+  // alpha dL/dalpha = T alpha dL/dC . c - alpha / (1 - alpha) dL/dC . (colour behind)
+  behind_terms<K>(W.D, q, f, W.one);
+#pragma unroll
+  for (int j = 0; j < 4; j++) {
+    const float dx = G.dx[(4 * K + j) & 7];
+    float w = q[j];
+    if constexpr (FORM == kExact) w = e[j] <= kAlphaMax ? w : 0.f;  // zero derivative above the clamp
+    const float w1 = w * dx;
+    G.s0[h] += w;
+    G.s1[h] += w1;
+    G.s2[h] = __fmaf_rn(w1, dx, G.s2[h]);
+  }
+}
+
+template <BwdForm FORM>
+__device__ __forceinline__ void bwd_group(BwdWave& W, BwdGauss& G, float col) {
+  // keeps the forms' exponents apart: formed ahead of the choice between
+  // them, all sixteen would be held in registers
+  asm volatile("" : "+v"(G.cA));
+  bwd_steps<0, FORM>(W, G, col);
+  bwd_steps<1, FORM>(W, G, col);
+  bwd_steps<2, FORM>(W, G, col);
+  bwd_steps<3, FORM>(W, G, col);
 }
 
 // One work item = one chunk of `chunk` list positions of one tile, walked
 // back to front from the state the forward saved where the next chunk begins
 // (or from the pixel's final state for the tile's last chunk).
-// Seven wavefronts per SIMD (72 registers, no spills; one 800x800 view of
-// 300k Gaussians: 192 -> 190 us).
-template <int TW>
-__global__ void __launch_bounds__(kBlock, 7) k_blend_bwd(ViewTable vt, DevSettings ds, const Rec* __restrict__ rec,
-                                                      const uint2* __restrict__ ranges,
-                                                      const uint32_t* __restrict__ pval, BlendState bs,
-                                                      float* __restrict__ g2d, int batch) {
-  __shared__ BatchLDS L;
-  __shared__ float s_g[kG2D][kBlock];  // per staged Gaussian, summed over the four wavefronts
+//
+// Bound by the vector instructions it issues.  With a pixel per lane for the
+// whole walk, a Gaussian cost 65 of them, 24 for the sums of its nine values
+// over the wavefront; here a group of 16 takes 31 a step and Gaussian without
+// a reduction (the product dL/dC . c is four f32 matrix products a group, which
+// share the vector units' rate but replace 48 instructions by 32 issue slots;
+// the colour sums are cheaper as vector instructions: 3465 against 3780 us
+// with matrix products on sixteen uneven views of 500k Gaussians).  Vector
+// instructions there 2.81 -> 1.6 G, time 4796 -> 3410 us; one 800x800 view of
+// 300k Gaussians 228 -> 169 us; eight 1080p views of 1M: step 8.50 -> 7.07 ms.
+// Registers: 95 hold the walk without spills, five wavefronts per SIMD; six
+// (80, a few spilled outside the steps) are 2% faster where the launch has
+// many long lists (MAXB = 256) and 8% slower on one 403x301 view.
+template <int TW, int MAXB>
+__global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
+    k_blend_bwd(ViewTable vt, DevSettings ds, const Rec* __restrict__ rec, const uint2* __restrict__ ranges,
+                const uint32_t* __restrict__ pval, BlendState bs, float* __restrict__ g2d, int batch) {
+  __shared__ BatchLDS<MAXB> L;
+  __shared__ float s_g[kG2D * MAXB];  // per staged Gaussian, summed over the four wavefronts
   __shared__ uint32_t s_maxlast;
   // the list holds the items in the order the forward's tiles finished
   // (measured: 5 us faster on c2 than taking it from the back, the long
@@ -503,15 +638,21 @@ __global__ void __launch_bounds__(kBlock, 7) k_blend_bwd(ViewTable vt, DevSettin
   const ViewDesc& vd = vt.v[vi];
   const int local = tile - vd.tile_base;
   const int tx = local % vd.ntx, ty = local / vd.ntx;
-  const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int wv = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  const int gj = l & 15, row = l >> 4;
   const float ox = (float)(tx * TW) + 0.5f, oy = (float)(ty * TileMap<TW>::TH) + 0.5f;
   const int px = tx * TW + TileMap<TW>::bx(wv) + (l & 7);
   const int py = ty * TileMap<TW>::TH + TileMap<TW>::by(wv) + (l >> 3);
   const bool inside = px < vd.W && py < vd.H;
-  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
-  const uint32_t* list4 = reinterpret_cast<const uint32_t*>(L.list[wv]);
+  // pixel centres of the wavefront's block: its columns, and the row's first line
+  float fx[8];
+#pragma unroll
+  for (int k = 0; k < 8; k++)
+    fx[k] = __uint_as_float(__builtin_amdgcn_readfirstlane(
+        __float_as_uint((float)(tx * TW + TileMap<TW>::bx(wv) + k) + 0.5f)));
+  const float by0 = (float)(ty * TileMap<TW>::TH + TileMap<TW>::by(wv) + 2 * row) + 0.5f;
 
-  float Tf = 1.f, dC0 = 0.f, dC1 = 0.f, dC2 = 0.f;
+  float Tf = 0.f, dC0 = 0.f, dC1 = 0.f, dC2 = 0.f;
   uint32_t last = 0;
   if (inside) {
     const int64_t HW = (int64_t)vd.W * vd.H;
@@ -522,109 +663,115 @@ __global__ void __launch_bounds__(kBlock, 7) k_blend_bwd(ViewTable vt, DevSettin
     dC1 = vd.dimg[HW + pix];
     dC2 = vd.dimg[2 * HW + pix];
   }
+  // dL/dC passes through the (not yet used) staging records into the operand
+  // of dL/dC . c
+  static_assert(sizeof(L.rec) >= sizeof(float4) * kBlock, "dL/dC fits the staged records");
+  float4* s_dc = reinterpret_cast<float4*>(L.rec);
+  s_dc[threadIdx.x] = make_float4(dC0, dC1, dC2, 0.f);
   if (threadIdx.x == 0) s_maxlast = 0;
-#pragma unroll
-  for (int k = 0; k < kG2D; k++) s_g[k][threadIdx.x] = 0.f;
+  for (int k = threadIdx.x; k < kG2D * MAXB; k += kBlock) s_g[k] = 0.f;
   __syncthreads();
   const uint32_t wlast = __builtin_amdgcn_readfirstlane(wave_max(last));
   if (l == 0) atomicMax(&s_maxlast, wlast);
+  BwdWave W;
+  W.dC[0] = dC0;
+  W.dC[1] = dC1;
+  W.dC[2] = dC2;
+  {
+    const float* q = reinterpret_cast<const float*>(s_dc + wv * 64);
+    // operand lane (i, k) = (l & 15, l >> 4): result row / column i, contraction index k
+#pragma unroll
+    for (int k = 0; k < 4; k++) W.dcA[k] = q[4 * ((gj >> 2) * 16 + 4 * k + (gj & 3)) + row];
+#pragma unroll
+    for (int j = 0; j < 4; j++) W.one[j] = (l & 3) == j ? 1.f : 0.f;
+  }
   __syncthreads();
   const uint2 rg = ranges[tile];
   const uint32_t maxlast = s_maxlast;
   // state behind the chunk: transmittance T in front of it and the colour S
-  // behind it (background included), carried as D = dL/dC . S
-  float T = Tf;
+  // behind it (background included), carried as D = dL/dC . S.  A pixel
+  // outside the image has T = 0 and dL/dC = 0: it adds exact zeros.
   float S0 = Tf * ds.bg[0], S1 = Tf * ds.bg[1], S2 = Tf * ds.bg[2];
+  W.T = Tf;
   if (cstart + chunk < last) {
     // the pixel takes Gaussians past this chunk: resume from the state saved
     // where the next chunk begins (otherwise its final state is that state)
     const int64_t slot = ((int64_t)rg.x + cstart + chunk) >> bs.chunk_shift;
     const float4 st = slot < bs.nbound ? bs.bound[slot * kBlock + threadIdx.x] : make_float4(1.f, 0.f, 0.f, 0.f);
-    T = st.x;
+    W.T = st.x;
     S0 += st.y;
     S1 += st.z;
     S2 += st.w;
   }
-  float D = dC0 * S0 + dC1 * S1 + dC2 * S2;
+  W.D = dC0 * S0 + dC1 * S1 + dC2 * S2;
+  // The walk of a pixel stops before its transmittance would fall below 1e-4,
+  // which takes alpha <= 0.99 from at most 1e-2: a pixel that ended above
+  // that took every Gaussian that reaches 1/255 there, so only the others
+  // compare list positions.
+  W.lastcmp = (Tf > 0.0101f || !inside) ? 0xFFFFFFFFu : last;
+  uint32_t minlast = ~wave_max(~W.lastcmp);
+  minlast = __builtin_amdgcn_readfirstlane(minlast);
   const uint32_t cend = min(cstart + chunk, maxlast);
   const float kq = -0.5f * kLog2e;
 
   for (uint32_t bend = rg.x + cend; bend > rg.x + cstart;) {
     const uint32_t b0 = (bend - (rg.x + cstart) > (uint32_t)batch) ? bend - batch : rg.x + cstart;
     const uint32_t nb = bend - b0;
-    const uint32_t wn = stage_batch<TW>(L, rec, pval, b0, nb, ox, oy);
+    const uint32_t wn = stage_batch<TW, MAXB>(L, rec, pval, b0, nb, ox, oy);
     const uint32_t pos0 = b0 - rg.x;
-    // groups of four list slots, from the back
-    const uint32_t lw = list4[l];
-    const int ng = (int)((wn + 3) >> 2);
-    // A group of four list slots, back to front.  What does not depend on the
-    // walk's state -- offsets, exponent, take flag -- is formed for all four
-    // first, branch-free; alpha and 1 / (1 - alpha) only for a pair some lane
-    // takes (c2 backward 209 -> 206 us); then the reverse steps run in pairs, each pair's
-    // 18 per-lane values summed in one straight-line reduction (a Gaussian no
-    // lane took adds zeros; a pair no lane took is skipped).  The one
-    // reduction for both needs no register copies for the in-place lane
-    // swaps, which a choice between a joint and two single reductions did.
-    auto grad = [&](const Group4& G, int g) {
-      float dxs[4], dys[4], ars[4], as[4], ros[4];  // ars: the exponent until the pair is taken
-      bool cs[4];
+    for (int g = (int)((wn + 15) >> 4) - 1; g >= 0; g--) {
+      // lane j takes list slot 16 g + j; past the list a Gaussian that no pixel takes
+      const uint32_t i = 16 * (uint32_t)g + gj;
+      const uint32_t slot = L.list[wv][min(i, wn - 1)];
+      BwdGauss G;
+      G.pos = pos0 + slot;
+      if (__builtin_amdgcn_readfirstlane(G.pos) >= wlast) continue;  // behind every pixel's last
+      const Staged& sr = L.rec[slot];
+      const float4 A = sr.a;
+      const float2 B = make_float2(sr.b.x, i < wn ? sr.b.y : -1e30f);
+      const float col = reinterpret_cast<const float*>(&sr.c)[row];  // channel `row` (the fourth is 0)
+      G.cA = A.z;
 #pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const uint32_t pos = pos0 + G.j[u];
-        // slots past the list and Gaussians no pixel of this wavefront reached are out
-        const bool in = (uint32_t)(4 * g + u) < wn && pos < wlast;
-        dxs[u] = fx - G.a[u].x;
-        dys[u] = fy - G.a[u].y;
-        const float p = log2_alpha(G.a[u], make_float4(G.b[u].x, G.b[u].y, 0.f, 0.f), dxs[u], dys[u]);
-        cs[u] = in && pos < last && p >= kLog2AlphaMin;
-        ars[u] = p;
+      for (int k = 0; k < 8; k++) G.dx[k] = fx[k] - A.x;
+      float dy[2];
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        dy[h] = (by0 + (float)h) - A.y;
+        G.bdy[h] = __fmul_rn(A.w, dy[h]);
+        G.cdy[h] = __fmaf_rn(__fmul_rn(B.x, dy[h]), dy[h], B.y);
+        G.s0[h] = G.s1[h] = G.s2[h] = 0.f;
       }
-      // one reverse step: updates T and D and fills the per-lane values to sum
-      auto step = [&](int u, float (&gv)[kG2D]) {
-        const bool contrib = cs[u];
-        const float a = as[u], ro = ros[u], dx = dxs[u], dy = dys[u];
-        const float Tb = T * ro;  // transmittance in front of this Gaussian (T where not taken)
-        const float wgt = a * Tb;
-        const float dc = dC0 * G.c[u].x + dC1 * G.c[u].y + dC2 * G.c[u].z;
-        const float dl_da = Tb * dc - ro * D;  // dL/dC . (c T_front - S_behind / (1 - alpha))
-        D += dc * wgt;
-        T = Tb;
-        // d alpha / d(exponent) = alpha while alpha is below its clamp, zero above
-        const float dl_dp = (contrib && ars[u] <= kAlphaMax) ? dl_da * ars[u] : 0.f;
-        const float e0 = dl_dp * dx, e1 = dl_dp * dy;
-        // moments of dL/d(exponent) over the lanes; the mean and opacity gradients
-        // are formed from them once per Gaussian after the reduction
-        gv[0] = e0;
-        gv[1] = e1;
-        gv[2] = e0 * dx;
-        gv[3] = e0 * dy;
-        gv[4] = e1 * dy;
-        gv[5] = dl_dp;
-        gv[6] = dC0 * wgt;
-        gv[7] = dC1 * wgt;
-        gv[8] = dC2 * wgt;
-      };
-#pragma unroll
-      for (int h = 1; h >= 0; h--) {
-        if (__ballot(cs[2 * h + 1] || cs[2 * h]) == 0) continue;
-#pragma unroll
-        for (int u = 2 * h; u < 2 * h + 2; u++) {
-          ars[u] = exp2_fast(ars[u]);
-          // a lane that does not take the Gaussian gets alpha 0: 1 / (1 - 0) is
-          // exactly 1, so its step leaves T and D exactly as they are
-          as[u] = fminf(cs[u] ? kAlphaMax : 0.f, ars[u]);
-          ros[u] = rcp_fast(1.0f - as[u]);
-        }
-        float ga[kG2D], gb[kG2D];
-        step(2 * h + 1, ga);
-        step(2 * h, gb);
-        wave_sum18_to_lds(ga, gb, s_g, (int)G.j[2 * h + 1], (int)G.j[2 * h], l);
+      G.col[0] = G.col[1] = G.col[2] = 0.f;
+      // alpha stays below its clamp where alpha_cond does (log2 0.99 = -0.0145)
+      if (__ballot(B.y > -0.0146f))
+        bwd_group<kExact>(W, G, col);
+      else if (__ballot(G.pos >= minlast))
+        bwd_group<kStops>(W, G, col);
+      else
+        bwd_group<kFree>(W, G, col);
+      // the moments of w about the Gaussian's centre and the colour gradient,
+      // summed over the four rows (halving exchanges) and added in LDS
+      const float v[kG2D] = {G.s1[0] + G.s1[1],
+                             dy[0] * G.s0[0] + dy[1] * G.s0[1],
+                             G.s2[0] + G.s2[1],
+                             dy[0] * G.s1[0] + dy[1] * G.s1[1],
+                             dy[0] * dy[0] * G.s0[0] + dy[1] * dy[1] * G.s0[1],
+                             G.s0[0] + G.s0[1],
+                             G.col[0],
+                             G.col[1],
+                             G.col[2]};
+      const float k0 = swap16_add(swap32_add(v[0], v[1]), swap32_add(v[2], v[3]));
+      const float k1 = swap16_add(swap32_add(v[4], v[5]), swap32_add(v[6], v[7]));
+      const float h8 = swap32_add(v[8], v[8]);
+      const float k2 = swap16_add(h8, h8);
+      if (i < wn) {
+        // rows 0 .. 3 of k0 hold v0 v2 v1 v3, of k1 v4 v6 v5 v7, every row of k2 v8
+        float* const to = s_g + slot * kG2D;
+        const int f = row == 0 ? 0 : row == 1 ? 2 : row == 2 ? 1 : 3;
+        atomicAdd(to + f, k0);
+        atomicAdd(to + f + 4, k1);
+        if (row == 0) atomicAdd(to + 8, k2);
       }
-    };
-    for (int g = ng - 1; g >= 0; g--) {
-      Group4 X;
-      fetch_group(L, lw, (uint32_t)g, wn, X);
-      grad(X, g);
     }
     __syncthreads();
     // one set of global atomics per (chunk, Gaussian).  Each staged
@@ -635,35 +782,32 @@ __global__ void __launch_bounds__(kBlock, 7) k_blend_bwd(ViewTable vt, DevSettin
     // memory request per row instead of one per component), zero components
     // skipped.
     const int t = threadIdx.x;
-    static_assert(sizeof(L.list) >= sizeof(uint32_t) * kBlock, "entry ids fit the slot lists");
+    static_assert(sizeof(L.list) >= sizeof(uint32_t) * MAXB, "entry ids fit the slot lists");
     uint32_t* s_ent = reinterpret_cast<uint32_t*>(L.list);  // the slot lists are no longer read
     if ((uint32_t)t < nb) {
       float v[kG2D];
 #pragma unroll
-      for (int k = 0; k < kG2D; k++) v[k] = s_g[k][t];
+      for (int k = 0; k < kG2D; k++) v[k] = s_g[t * kG2D + k];
       // exponent p2 = log2(alpha) = cA dx^2 + cB dx dy + cC dy^2 + log2(alpha_cond), with
       // dx = x - u: dp2/du = -(2 cA dx + cB dy), dp2/dv = -(cB dx + 2 cC dy); and
       // dp2/dcA = dx^2 etc., cA = kq Qxx, cB = 2 kq Qxy, cC = kq Qyy
       const Staged& sr = L.rec[t];
       const float m0 = v[0] * kLn2, m1 = v[1] * kLn2;  // moments of dL/dp2 = dL/dp ln 2
-      s_g[0][t] = -(2.f * sr.a.z * m0 + sr.a.w * m1);
-      s_g[1][t] = -(sr.a.w * m0 + 2.f * sr.b.x * m1);
-      s_g[2][t] = v[2] * (kLn2 * kq);
-      s_g[3][t] = v[3] * (kLn2 * kq);
-      s_g[4][t] = v[4] * (kLn2 * kq);
-      s_g[5][t] = v[5] * sr.b.z;  // d alpha / d alpha_cond = alpha / alpha_cond
+      s_g[t * kG2D + 0] = -(2.f * sr.a.z * m0 + sr.a.w * m1);
+      s_g[t * kG2D + 1] = -(sr.a.w * m0 + 2.f * sr.b.x * m1);
+      s_g[t * kG2D + 2] = v[2] * (kLn2 * kq);
+      s_g[t * kG2D + 3] = v[3] * (kLn2 * kq);
+      s_g[t * kG2D + 4] = v[4] * (kLn2 * kq);
+      s_g[t * kG2D + 5] = v[5] * sr.b.z;  // d alpha / d alpha_cond = alpha / alpha_cond
       s_ent[t] = __float_as_uint(sr.b.w);
     }
     __syncthreads();
 #pragma unroll 1
-    for (int r = 0; r < kG2D; r++) {
-      const uint32_t idx = (uint32_t)(r * kBlock + t);
-      if (idx < nb * kG2D) {
-        const uint32_t jg = idx / kG2D, k = idx - jg * kG2D;
-        const float val = s_g[k][jg];
-        s_g[k][jg] = 0.f;
-        if (val != 0.f) unsafeAtomicAdd(g2d + (int64_t)s_ent[jg] * kG2D + k, val);
-      }
+    for (uint32_t idx = t; idx < nb * kG2D; idx += kBlock) {
+      const uint32_t jg = idx / kG2D, k = idx - jg * kG2D;
+      const float val = s_g[idx];
+      s_g[idx] = 0.f;
+      if (val != 0.f) unsafeAtomicAdd(g2d + (int64_t)s_ent[jg] * kG2D + k, val);
     }
     __syncthreads();
     bend = b0;
@@ -700,14 +844,25 @@ void launch_blend_fwd(const ViewTable& vt, const DevSettings& s, const Rec* rec,
     launch_fwd<true, false>(vt, s, rec, ranges, pval, bs, st);
 }
 
+namespace {
+template <int TW>
+void launch_bwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges, const uint32_t* pval,
+                const BlendState& bs, float* g2d, int batch, dim3 grid, hipStream_t st) {
+  if (batch <= 128)
+    hipLaunchKernelGGL((k_blend_bwd<TW, 128>), grid, dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs, g2d, batch);
+  else
+    hipLaunchKernelGGL((k_blend_bwd<TW, 256>), grid, dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs, g2d, batch);
+}
+}  // namespace
+
 void launch_blend_bwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges,
                       const uint32_t* pval, BlendState bs, float* g2d, int batch, int64_t items, hipStream_t st) {
   if (vt.total_tiles <= 0 || items <= 0) return;
   const dim3 grid((unsigned)items);
   switch (vt.tile_w) {
-    case 8: hipLaunchKernelGGL(k_blend_bwd<8>, grid, dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs, g2d, batch); break;
-    case 32: hipLaunchKernelGGL(k_blend_bwd<32>, grid, dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs, g2d, batch); break;
-    default: hipLaunchKernelGGL(k_blend_bwd<16>, grid, dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs, g2d, batch); break;
+    case 8: launch_bwd<8>(vt, s, rec, ranges, pval, bs, g2d, batch, grid, st); break;
+    case 32: launch_bwd<32>(vt, s, rec, ranges, pval, bs, g2d, batch, grid, st); break;
+    default: launch_bwd<16>(vt, s, rec, ranges, pval, bs, g2d, batch, grid, st); break;
   }
 }
 
