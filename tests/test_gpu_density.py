@@ -108,3 +108,49 @@ def test_training_continues_after_densify():
     assert tr.lambda_raw.shape[0] == n_new and tr.m.shape[1] == n_new
     losses = [float(tr.step([cam], tgt)) for _ in range(3)]
     assert all(math.isfinite(x) for x in losses)
+
+
+@pytest.mark.parametrize("n", [1, 63, 255, 256, 257, 700])
+@pytest.mark.parametrize("kind", ["keep", "clone", "split", "mixed"])
+@pytest.mark.parametrize("moments", [False, True])
+def test_density_apply_block_edges(n, kind, moments):
+    """The apply lists up to two outputs for each of 256 parents per workgroup:
+    one Gaussian, whole and cut workgroups, no and only doubled outputs.
+    Copies are bitwise, children within float32 rounding (as above)."""
+    from paper_2410_04974_amd import Renderer
+    pn = _scene(n, 41)
+    rng = np.random.default_rng(42)
+    pn[75] = 1.0
+    grow = {"keep": np.zeros(n, bool), "clone": np.ones(n, bool), "split": np.ones(n, bool),
+            "mixed": rng.random(n) < 0.6}[kind]
+    if kind == "mixed":
+        pn[75, rng.random(n) < 0.3] = -6.0
+    stats = np.stack([np.where(grow, 5e-4, 5e-5), np.ones(n)]).astype(np.float32)
+    _, So = oracle.decompose(pn)
+    smax = np.sort(So.max(axis=1))
+    pdense = {"keep": 1.0, "clone": 1e3, "split": 1e-6}.get(kind)
+    if pdense is None:
+        i = int(np.argmax(np.diff(smax))) if n > 1 else 0
+        pdense = float(0.5 * (smax[i] + smax[min(i + 1, n - 1)])) if n > 1 else 1.0
+    noise = rng.normal(size=(2, 3, n)).astype(np.float32)
+    m, v = (rng.normal(size=(76, n)).astype(np.float32) for _ in range(2))
+    d, _ = oracle.decisions(pn, stats, 2e-4, pdense, 1.0, 0.01)
+    sizes = np.array([0, 1, 2, 2])[d]
+    if sizes.sum() == 0:
+        pytest.skip("every Gaussian pruned")
+    ref = oracle.densify(pn, stats, noise, 2e-4, pdense, 1.0, 0.01, m=m, v=v)
+    mom = dict(m=G.to_dev(m), v=G.to_dev(v)) if moments else {}
+    po, mo, vo, _ = Renderer().ctx.densify(G.to_dev(pn), torch.from_numpy(stats).to(G.DEV),
+                                           torch.from_numpy(noise).to(G.DEV), 2e-4, pdense, 1.0, 0.01, **mom)
+    po = po.cpu().numpy()
+    assert po.shape == ref["params"].shape
+    if moments:
+        assert np.array_equal(mo.cpu().numpy(), ref["m"].astype(np.float32))
+        assert np.array_equal(vo.cpu().numpy(), ref["v"].astype(np.float32))
+    parent, split = np.repeat(np.arange(n), sizes), np.repeat(d == 3, sizes)
+    assert np.array_equal(po[:, ~split], pn[:, parent[~split]])
+    if split.any():
+        diff = np.abs(po[:, split] - ref["params"][:, split])
+        assert (diff[0:3] / So[parent[split]].max(axis=1)).max() < 1e-3
+        assert diff[6:].max() < 1e-4
+        assert np.array_equal(po[3:6, split], pn[3:6, parent[split]])
