@@ -22,17 +22,27 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kLog2AlphaMin = -7.994353436858858f;  // log2(1/255)
 constexpr int kWaves = kBlock / 64;
 
+// Whether a Gaussian's alpha can reach its clamp of 0.99 at some pixel.  Alpha
+// is at most alpha_cond up to the rounding of the exponent, whose terms are up
+// to q_max / (1 - rho^2) large (rho: the conic's correlation): below
+// 1 / (1 - rho^2) = 1000 they round by under 3e-3, or 0.2% of alpha.
+__device__ __forceinline__ bool may_clamp(float alpha_cond, float qxx, float qxy, float qyy) {
+  return alpha_cond > 0.985f || qxy * qxy > 0.999f * qxx * qyy;
+}
+
 // Staged record: the conic pre-scaled so that alpha exp(-q/2) = exp2(p2 + log2 alpha).
 struct Staged {
   float4 a;  // u, v, cA = -log2e/2 Qxx, cB = -log2e Qxy
-  float4 b;  // cC = -log2e/2 Qyy, log2(alpha_cond), 1/alpha_cond, entry id (bits)
+  float4 b;  // cC = -log2e/2 Qyy, log2(alpha_cond), 1/alpha_cond (negated: may_clamp), entry id (bits)
   float4 c;  // r, g, b, -
 };
 
 __device__ __forceinline__ Staged stage(const Rec& r, uint32_t e) {
   Staged s;
   s.a = make_float4(r.a.x, r.a.y, -0.5f * kLog2e * r.a.z, -kLog2e * r.a.w);
-  s.b = make_float4(-0.5f * kLog2e * r.b.x, __log2f(r.b.y), __builtin_amdgcn_rcpf(r.b.y), __uint_as_float(e));
+  const float ia = __builtin_amdgcn_rcpf(r.b.y);
+  s.b = make_float4(-0.5f * kLog2e * r.b.x, __log2f(r.b.y), may_clamp(r.b.y, r.a.z, r.a.w, r.b.x) ? -ia : ia,
+                    __uint_as_float(e));
   s.c = make_float4(r.c.x, r.c.y, r.c.z, 0.f);
   return s;
 }
@@ -729,6 +739,7 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
       const Staged& sr = L.rec[slot];
       const float4 A = sr.a;
       const float2 B = make_float2(sr.b.x, i < wn ? sr.b.y : -1e30f);
+      const bool clamps = sr.b.z < 0.f;
       const float col = reinterpret_cast<const float*>(&sr.c)[row];  // channel `row` (the fourth is 0)
       G.cA = A.z;
 #pragma unroll
@@ -742,8 +753,7 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
         G.s0[h] = G.s1[h] = G.s2[h] = 0.f;
       }
       G.col[0] = G.col[1] = G.col[2] = 0.f;
-      // alpha stays below its clamp where alpha_cond does (log2 0.99 = -0.0145)
-      if (__ballot(B.y > -0.0146f))
+      if (__ballot(clamps))
         bwd_group<kExact>(W, G, col);
       else if (__ballot(G.pos >= minlast))
         bwd_group<kStops>(W, G, col);
@@ -798,7 +808,7 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
       s_g[t * kG2D + 2] = v[2] * (kLn2 * kq);
       s_g[t * kG2D + 3] = v[3] * (kLn2 * kq);
       s_g[t * kG2D + 4] = v[4] * (kLn2 * kq);
-      s_g[t * kG2D + 5] = v[5] * sr.b.z;  // d alpha / d alpha_cond = alpha / alpha_cond
+      s_g[t * kG2D + 5] = v[5] * fabsf(sr.b.z);  // d alpha / d alpha_cond = alpha / alpha_cond
       s_ent[t] = __float_as_uint(sr.b.w);
     }
     __syncthreads();

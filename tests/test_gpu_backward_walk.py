@@ -59,3 +59,23 @@ def test_backward_walk_forms(n, batch, chunk, tile, opacity):
     assert np.isfinite(g).all()
     assert all(v < 1e-3 for v in errs.values())
     assert all(v <= 1.0 for v in el.values())
+
+
+@pytest.mark.parametrize("opacity", [0.5, 0.98])
+def test_needles_stay_finite(opacity):
+    """Gaussians so long and thin that the float32 exponent can come out above 0
+    next to their axis: alpha stays below its clamp in both directions."""
+    p = stack(40, "dense")
+    for k, v in zip(synth.DIAG_SPATIAL, (3.5, -4.0, -4.0)):
+        p[synth.ROW_L + k] = v + 0.01 * np.arange(40)
+    p[synth.ROW_OPACITY] = np.log(opacity / (1 - opacity))
+    cam = synth.default_camera(301, 203)
+    r, pt, imgs = G.render(p, [cam])
+    from paper_2410_04974_amd import _lib
+    T = r.ctx.export(_lib.EXPORT_T_FINAL)
+    rec, tiles = G.records(r)
+    q = rec[tiles > 0]
+    assert (q[:, G.REC_QXY] ** 2 > 0.999 * q[:, G.REC_QXX] * q[:, G.REC_QYY]).sum() >= 10
+    g = r.backward(pt, [torch.from_numpy(synth.upstream_gradient([cam])[0]).to(G.DEV)])
+    assert T.min() > 0 and T.max() <= 1 and np.isfinite(imgs[0]).all()
+    assert torch.isfinite(g).all()
