@@ -282,10 +282,6 @@ DevSettings dev_settings(const sixdgs_settings& s) {
   return d;
 }
 
-// from this many tiles on, the automatic backward chunk and batch depth are
-// the long ones
-constexpr int64_t kAutoTiles = 16384;
-
 bool ensure_entries(sixdgs_ctx* c, int64_t E) {
   const int64_t e1 = E > 0 ? E : 1;
   return c->rec.ensure(e1) && c->tiles.ensure(e1) && c->dkey0.ensure(e1) && c->dkey1.ensure(e1) &&
@@ -708,7 +704,7 @@ sixdgs_status forward_impl(sixdgs_ctx* c, const float* params, const float* cach
   // the restarts (measured: 128 / 128 best for one 800x800 view, 256 / 512
   // for eight or sixteen 1080p-class views)
   {
-    const bool few = vt.total_tiles < kAutoTiles;
+    const bool few = few_tiles(vt.total_tiles);
     int chunk = c->s.chunk ? c->s.chunk : (few ? 128 : 512);
     int batch = c->s.batch ? c->s.batch : (few ? 128 : 256);
     if (batch > chunk) batch = chunk;

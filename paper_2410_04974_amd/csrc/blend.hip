@@ -12,6 +12,8 @@
 // (a tile's blocks differ in depth complexity, and a shared batch would hold
 // every wavefront to the slowest); the backward stages one LDS batch for the
 // workgroup and builds the four per-block lists from it.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace sixdgs {
@@ -195,16 +197,85 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// A pixel's running state in the forward.
+struct FwdPixel {
+  float T = 1.0f, C[3] = {0.f, 0.f, 0.f};
+  float K[3] = {0.f, 0.f, 0.f};  // colour of the current chunk alone
+  uint32_t last = 0, cnt = 0;
+};
+
+// One Gaussian of exponent p, (clamped) alpha a, colour c and 1-based list
+// position pos, for the pixels of `live` that take it (p >= log2(1/255)): the
+// weight a T enters the colour and T becomes T (1 - a), or the pixel stops and
+// leaves `live` where that would fall below 1e-4.  Written over the execution
+// mask: the two compares narrow it, so nothing after them needs a select
+// (a select costs as much as a compare here, 4.3 cycles per wavefront and
+// SIMD against 2.5 for the moves, products and sums).
+// CHUNK: also the chunk's own colour.
+template <bool SAVE, bool COUNTS, bool CHUNK>
+__device__ __forceinline__ void blend_one(FwdPixel& P, uint64_t& live, float p, float a, const float4& c) {
+  float Tn, w;
+  uint64_t take;
+  // (all lanes are active around this)
+#define SIXDGS_TAKE                              \
+  "s_mov_b64 exec, %[live]\n\t"                  \
+  "v_cmpx_le_f32_e64 %[take], %[pmin], %[p]\n\t" \
+  "v_fma_f32 %[tn], -%[T], %[a], %[T]\n\t"       \
+  "v_mul_f32_e32 %[w], %[a], %[T]\n\t"           \
+  "v_cmpx_le_f32_e32 vcc, %[tmin], %[tn]\n\t"    \
+  "v_fmac_f32_e32 %[c0], %[r], %[w]\n\t"         \
+  "v_fmac_f32_e32 %[c1], %[g], %[w]\n\t"         \
+  "v_fmac_f32_e32 %[c2], %[b], %[w]\n\t"         \
+  "v_mov_b32_e32 %[T], %[tn]\n\t"                \
+  "s_xor_b64 %[take], %[take], vcc\n\t"          \
+  "s_xor_b64 %[live], %[live], %[take]\n\t"
+#define SIXDGS_END "s_mov_b64 exec, -1"
+#define SIXDGS_IO                                                                                              \
+  [T] "+v"(P.T), [c0] "+v"(P.C[0]), [c1] "+v"(P.C[1]), [c2] "+v"(P.C[2]), [live] "+s"(live), [take] "=&s"(take), \
+      [tn] "=&v"(Tn), [w] "=&v"(w)
+#define SIXDGS_IN                                                                                          \
+  [p] "v"(p), [a] "v"(a), [r] "v"(c.x), [g] "v"(c.y), [b] "v"(c.z), [pmin] "s"(kLog2AlphaMin), [tmin] "s"(kTMin)
+  if constexpr (!SAVE) {
+    asm volatile(SIXDGS_TAKE SIXDGS_END : SIXDGS_IO : SIXDGS_IN : "vcc", "scc");
+  } else if constexpr (!CHUNK) {
+    asm volatile(SIXDGS_TAKE "v_mov_b32_e32 %[last], %[pos]\n\t" SIXDGS_END
+                 : SIXDGS_IO, [last] "+v"(P.last)
+                 : SIXDGS_IN, [pos] "v"(c.w)
+                 : "vcc", "scc");
+  } else {
+    asm volatile(SIXDGS_TAKE
+                 "v_fmac_f32_e32 %[k0], %[r], %[w]\n\t"
+                 "v_fmac_f32_e32 %[k1], %[g], %[w]\n\t"
+                 "v_fmac_f32_e32 %[k2], %[b], %[w]\n\t"
+                 "v_mov_b32_e32 %[last], %[pos]\n\t" SIXDGS_END
+                 : SIXDGS_IO, [last] "+v"(P.last), [k0] "+v"(P.K[0]), [k1] "+v"(P.K[1]), [k2] "+v"(P.K[2])
+                 : SIXDGS_IN, [pos] "v"(c.w)
+                 : "vcc", "scc");
+  }
+#undef SIXDGS_TAKE
+#undef SIXDGS_END
+#undef SIXDGS_IO
+#undef SIXDGS_IN
+  // (positions count from 1; the filler past the list has 0)
+  if constexpr (COUNTS) P.cnt += P.last != 0 && P.last == __float_as_uint(c.w) ? 1u : 0u;
+}
+
 // SAVE = false renders the image only (inference): no chunk boundaries, no
 // final transmittance, last contributor or chunk counts for a backward.
-// Five wavefronts per SIMD (96 registers, no spills): with tens of thousands
-// of tiles the walks' load latency is hidden by the extra wave (eight 1080p
-// views of 1M Gaussians: 1.87 -> 1.72 ms).
 // COUNTS additionally counts each pixel's contributors (a debug export).
-template <int TW, bool SAVE, bool COUNTS>
-__global__ void __launch_bounds__(kBlock, 5) k_blend_fwd(ViewTable vt, DevSettings ds, const Rec* __restrict__ rec,
-                                                      const uint2* __restrict__ ranges,
-                                                      const uint32_t* __restrict__ pval, BlendState bs) {
+// G: Gaussians whose records a step reads and whose exponents it forms at
+// once; WAVES: the wavefronts per SIMD to fit.  Bound by the vector
+// instructions where there are many tiles, which more wavefronts then keep
+// issuing: pairs and six wavefronts (80 registers) take 1352 us on sixteen
+// uneven views of 500k Gaussians, fours and four 1506; image only, 1408x1408 of
+// 12.7k Gaussians, pairs and seven 103, fours and five 107.  With few tiles the
+// longest walks bound it, and a step of four shortens them: one 800x800 view of
+// 300k, fours and four 134 us, pairs and six 141; 403x301 of 20k 34 and 38.
+// (By selects instead of the execution mask: 1622, 110, 152 and 38 us.)
+template <int TW, bool SAVE, bool COUNTS, int G, int WAVES>
+__global__ void __launch_bounds__(kBlock, WAVES) k_blend_fwd(ViewTable vt, DevSettings ds, const Rec* __restrict__ rec,
+                                                          const uint2* __restrict__ ranges,
+                                                          const uint32_t* __restrict__ pval, BlendState bs) {
   __shared__ FwdWaveLDS W[kWaves];
   __shared__ uint32_t s_maxlast, s_ibase;
   __shared__ float s_l1[kWaves];
@@ -231,60 +302,61 @@ __global__ void __launch_bounds__(kBlock, 5) k_blend_fwd(ViewTable vt, DevSettin
   const uint32_t n = rg.y - rg.x;
   const uint32_t* pv = pval + rg.x;
   const uint32_t chunk = bs.chunk;
-  float T = 1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
-  float K0 = 0.f, K1 = 0.f, K2 = 0.f;  // colour of the current chunk alone
-  uint32_t last = 0, cnt = 0, nbd = 0;
-  bool done = !inside;
+  FwdPixel P;
+  uint32_t nbd = 0;
+  uint64_t live = __ballot(inside);  // the pixels still composited
+  bool opaque = false;               // a pending Gaussian may reach alpha's clamp (uniform)
 
+  // CHUNK: the chunk's colour is wanted (past the first chunk: what lies
+  // behind a boundary never includes the first)
+  auto walk = [&](uint32_t nh, auto chunk_colour, auto clamp) {
+    for (uint32_t g = 0; G * g < nh && live; g++) {
+      float4 A[G], Cc[G];
+      float2 Bq[G];
+#pragma unroll
+      for (int u = 0; u < G; u++) {
+        A[u] = B.a[G * g + u];
+        Bq[u] = B.b[G * g + u];
+        Cc[u] = B.c[G * g + u];
+      }
+      // what does not depend on the pixel's state for all of the group first,
+      // so its records are read at once
+      float p[G], a[G];
+#pragma unroll
+      for (int u = 0; u < G; u++) {
+        p[u] = log2_alpha(A[u], make_float4(Bq[u].x, Bq[u].y, 0.f, 0.f), fx - A[u].x, fy - A[u].y);
+        a[u] = exp2_fast(p[u]);
+        if constexpr (decltype(clamp)::value) a[u] = fminf(kAlphaMax, a[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < G; u++)
+        blend_one<SAVE, COUNTS, decltype(chunk_colour)::value>(P, live, p[u], a[u], Cc[u]);
+    }
+  };
   auto composite = [&](uint32_t nh) {
     // the group that ends past nh would read stale slots: fill them with a
     // Gaussian no pixel takes (exponent -1e30) and a zero colour, so that
     // every slot of a group is evaluated alike
-    if ((uint32_t)l < ((4u - (nh & 3u)) & 3u)) {
+    if ((uint32_t)l < (G - nh % G) % G) {
       B.a[nh + l] = make_float4(0.f, 0.f, 0.f, 0.f);
       B.b[nh + l] = make_float2(0.f, -1e30f);
       B.c[nh + l] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     wave_lds_sync();
-    for (uint32_t g = 0; 4 * g < nh; g++) {
-      if (__ballot(!done) == 0) break;
-      float4 A[4], Cc[4];
-      float2 Bq[4];
-#pragma unroll
-      for (int u = 0; u < 4; u++) {
-        A[u] = B.a[4 * g + u];
-        Bq[u] = B.b[4 * g + u];
-        Cc[u] = B.c[4 * g + u];
-      }
-      // predicated rather than branched, also past the last slot, so the four
-      // records are read at once: the lanes of a wavefront rarely agree.  A
-      // Gaussian the pixel does not take gets alpha 0, which leaves T exactly
-      // as it is; T never falls below 1e-4 (it is only updated when the step
-      // does not stop), so such a step never stops either.
-#pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const float p = log2_alpha(A[u], make_float4(Bq[u].x, Bq[u].y, 0.f, 0.f), fx - A[u].x, fy - A[u].y);
-        const bool take = !done && p >= kLog2AlphaMin;
-        // the clamp doubles as the mask: min(0, .) is 0 whatever the exponent gives
-        const float a = fminf(take ? kAlphaMax : 0.f, exp2_fast(p));
-        const float Tn = __fmaf_rn(-T, a, T);  // T (1 - a)
-        const bool stop = Tn < kTMin;
-        done = done || stop;
-        const bool took = take && !stop;  // the same as wgt != 0: a >= 1/255 and T >= 1e-4 when taken
-        const float wgt = took ? a * T : 0.f;
-        C0 += Cc[u].x * wgt;
-        C1 += Cc[u].y * wgt;
-        C2 += Cc[u].z * wgt;
-        T = stop ? T : Tn;
-        if constexpr (SAVE) {
-          K0 += Cc[u].x * wgt;
-          K1 += Cc[u].y * wgt;
-          K2 += Cc[u].z * wgt;
-          last = took ? __float_as_uint(Cc[u].w) : last;
-        }
-        if constexpr (COUNTS) cnt += took ? 1u : 0u;
-      }
+    using Yes = std::true_type;
+    using No = std::false_type;
+    if (SAVE && nbd > 0) {
+      if (opaque)
+        walk(nh, Yes{}, Yes{});
+      else
+        walk(nh, Yes{}, No{});
+    } else {
+      if (opaque)
+        walk(nh, No{}, Yes{});
+      else
+        walk(nh, No{}, No{});
     }
+    opaque = false;
   };
 
   // software pipeline: entry ids two steps ahead, records one step ahead
@@ -298,7 +370,7 @@ __global__ void __launch_bounds__(kBlock, 5) k_blend_fwd(ViewTable vt, DevSettin
   if (n > 0) r_cur = rec[e_cur];
   uint32_t nh = 0;  // pending hits in B (uniform)
   for (uint32_t s0 = 0; s0 < n; s0 += kFwdStep) {
-    if (__ballot(!done) == 0) break;
+    if (!live) break;
     const Rec r_nxt = rec[e_nxt];
     uint32_t e_nn = 0;
     if (s0 + 2 * kFwdStep + l < n) e_nn = pv[s0 + 2 * kFwdStep + l];
@@ -308,12 +380,13 @@ __global__ void __launch_bounds__(kBlock, 5) k_blend_fwd(ViewTable vt, DevSettin
       composite(nh);
       nh = 0;
       const int64_t slot = ((int64_t)rg.x + s0) >> bs.chunk_shift;
-      if (slot < bs.nbound) bs.bound[slot * kBlock + threadIdx.x] = make_float4(T, K0, K1, K2);
-      K0 = K1 = K2 = 0.f;
+      if (slot < bs.nbound) bs.bound[slot * kBlock + threadIdx.x] = make_float4(P.T, P.K[0], P.K[1], P.K[2]);
+      P.K[0] = P.K[1] = P.K[2] = 0.f;
       nbd++;
     }
     const bool hit = (s0 + l < n) && ellipse_hits(r_cur, bx0, by0);
     const uint64_t bal = __ballot(hit);
+    opaque = opaque || __ballot(hit && may_clamp(r_cur.b.y, r_cur.a.z, r_cur.a.w, r_cur.b.x)) != 0;
     if (hit) {
       const uint32_t k = nh + (uint32_t)__popcll(bal & lt);
       B.a[k] = make_float4(r_cur.a.x, r_cur.a.y, -0.5f * kLog2e * r_cur.a.z, -kLog2e * r_cur.a.w);
@@ -335,16 +408,15 @@ __global__ void __launch_bounds__(kBlock, 5) k_blend_fwd(ViewTable vt, DevSettin
     if (inside) {
       const int64_t HW = (int64_t)vd.W * vd.H;
       const int64_t pix = (int64_t)py * vd.W + px;
-      vd.img[pix] = C0 + T * ds.bg[0];
-      vd.img[HW + pix] = C1 + T * ds.bg[1];
-      vd.img[2 * HW + pix] = C2 + T * ds.bg[2];
+#pragma unroll
+      for (int c = 0; c < 3; c++) vd.img[c * HW + pix] = P.C[c] + P.T * ds.bg[c];
     }
     return;
   }
 
   // turn the per-chunk colours into the colour behind each boundary: sums of
   // positive terms from the back, so no cancellation against the total
-  float S0 = K0, S1 = K1, S2 = K2;
+  float S0 = P.K[0], S1 = P.K[1], S2 = P.K[2];
   for (uint32_t m = nbd; m >= 1; m--) {
     const int64_t slot = ((int64_t)rg.x + (int64_t)m * chunk) >> bs.chunk_shift;
     if (slot >= bs.nbound) continue;
@@ -360,12 +432,12 @@ __global__ void __launch_bounds__(kBlock, 5) k_blend_fwd(ViewTable vt, DevSettin
     const int64_t HW = (int64_t)vd.W * vd.H;
     const int64_t pix = (int64_t)py * vd.W + px;
     // the running sum, whose rounding does not depend on where chunks begin
-    const float o[3] = {C0 + T * ds.bg[0], C1 + T * ds.bg[1], C2 + T * ds.bg[2]};
+    const float o[3] = {P.C[0] + P.T * ds.bg[0], P.C[1] + P.T * ds.bg[1], P.C[2] + P.T * ds.bg[2]};
 #pragma unroll
     for (int c = 0; c < 3; c++) vd.img[c * HW + pix] = o[c];
-    bs.T_final[vd.pix_base + pix] = T;
-    bs.last[vd.pix_base + pix] = last;
-    if constexpr (COUNTS) bs.counts[vd.pix_base + pix] = cnt;
+    bs.T_final[vd.pix_base + pix] = P.T;
+    bs.last[vd.pix_base + pix] = P.last;
+    if constexpr (COUNTS) bs.counts[vd.pix_base + pix] = P.cnt;
     if (bs.l1_partial) {
       // the L1 loss of the step (Sec. 4.4, Sec. 5.1): dL/dI = sign(I - I*) / count
 #pragma unroll
@@ -382,7 +454,7 @@ __global__ void __launch_bounds__(kBlock, 5) k_blend_fwd(ViewTable vt, DevSettin
     for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off);
     if (l == 0) s_l1[wv] = l1;
   }
-  const uint32_t wlast = wave_max(last);
+  const uint32_t wlast = wave_max(P.last);
   if (l == 0) atomicMax(&s_maxlast, wlast);
   __syncthreads();
   // the tile's backward work items (tile, 0 .. nch - 1), appended to the list
@@ -826,32 +898,26 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
 
 }  // namespace
 
-template <bool SAVE, bool COUNTS>
-void launch_fwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges,
-                const uint32_t* pval, const BlendState& bs, hipStream_t st) {
-  const dim3 grid(vt.total_tiles);
-  switch (vt.tile_w) {
-    case 8:
-      hipLaunchKernelGGL((k_blend_fwd<8, SAVE, COUNTS>), grid, dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs);
-      break;
-    case 32:
-      hipLaunchKernelGGL((k_blend_fwd<32, SAVE, COUNTS>), grid, dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs);
-      break;
-    default:
-      hipLaunchKernelGGL((k_blend_fwd<16, SAVE, COUNTS>), grid, dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs);
-      break;
-  }
+namespace {
+template <int TW>
+void launch_fwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges, const uint32_t* pval,
+                const BlendState& bs, bool save, hipStream_t st) {
+  auto k = !save                       ? k_blend_fwd<TW, false, false, 2, 7>
+           : bs.counts                 ? k_blend_fwd<TW, true, true, 4, 4>
+           : few_tiles(vt.total_tiles) ? k_blend_fwd<TW, true, false, 4, 4>
+                                       : k_blend_fwd<TW, true, false, 2, 6>;
+  hipLaunchKernelGGL(k, dim3(vt.total_tiles), dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs);
 }
+}  // namespace
 
 void launch_blend_fwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges,
                       const uint32_t* pval, BlendState bs, int batch, bool save, hipStream_t st) {
   if (vt.total_tiles <= 0) return;
-  if (!save)
-    launch_fwd<false, false>(vt, s, rec, ranges, pval, bs, st);
-  else if (bs.counts)
-    launch_fwd<true, true>(vt, s, rec, ranges, pval, bs, st);
-  else
-    launch_fwd<true, false>(vt, s, rec, ranges, pval, bs, st);
+  switch (vt.tile_w) {
+    case 8: launch_fwd<8>(vt, s, rec, ranges, pval, bs, save, st); break;
+    case 32: launch_fwd<32>(vt, s, rec, ranges, pval, bs, save, st); break;
+    default: launch_fwd<16>(vt, s, rec, ranges, pval, bs, save, st); break;
+  }
 }
 
 namespace {
