@@ -232,7 +232,7 @@ std::string build_views(const sixdgs_settings& s, int64_t n, const sixdgs_camera
   vt.tile_shift_x = ilog2(s.tile_w);
   vt.tile_shift_y = ilog2(s.tile_h);
   vt.n = n;
-  int64_t tiles = 0;
+  int64_t tiles = 0, patches = 0;
   total_px = 0;
   for (int k = 0; k < ncam; k++) {
     const sixdgs_camera& c = cams[k];
@@ -260,12 +260,15 @@ std::string build_views(const sixdgs_settings& s, int64_t n, const sixdgs_camera
     d.ntx = (c.width + s.tile_w - 1) / s.tile_w;
     d.nty = (c.height + s.tile_h - 1) / s.tile_h;
     d.tile_base = (int32_t)tiles;
+    d.patch_base = (int32_t)patches;
     d.pix_base = total_px;
+    patches += (int64_t)((d.ntx + 7) / 8) * ((d.nty + 7) / 8);
     tiles += (int64_t)d.ntx * d.nty;
     total_px += (int64_t)c.width * c.height;
   }
   if (tiles >= (1ll << 24)) return "too many screen tiles";
   vt.total_tiles = (int32_t)tiles;
+  vt.total_patches = (int32_t)patches;
   if (n < 0) return "n must be >= 0";
   if (n * (int64_t)ncam >= (1ll << 32) - 1) return "n * ncam too large";
   return "";
@@ -291,7 +294,8 @@ bool ensure_entries(sixdgs_ctx* c, int64_t E) {
 bool ensure_scratch(sixdgs_ctx* c, int64_t E, int64_t pcap) {
   const int64_t e1 = std::max<int64_t>(E, 1);
   const int64_t p1 = std::max<int64_t>(pcap, 1);
-  return c->rstate.ensure(sort_state_words(e1, false) + sort_state_words(p1, true)) &&
+  return c->rstate.ensure(sort_state_words(e1, false) + sort_state_words(p1, true) +
+                          list_state_words(e1, c->vt.total_tiles, c->vt.total_patches)) &&
          c->blk_start.ensure(sort_block_starts(p1));
 }
 
@@ -342,6 +346,7 @@ void fill_sort_buffers(sixdgs_ctx* c, int64_t E) {
   b.blk_start = c->blk_start.p;
   b.nblk_start = c->blk_start.cap;
   b.total_tiles = c->vt.total_tiles;
+  b.total_patches = c->vt.total_patches;
   b.tile_order = c->tile_order.p;
   b.order_state = c->order_state.p;
   b.g2d = c->bin_g2d;
@@ -422,12 +427,12 @@ sixdgs_status prepare_binning(sixdgs_ctx* c, int64_t E) {
 sixdgs_status run_binning(sixdgs_ctx* c, int64_t E, bool prepped, hipStream_t st) {
   const bool fixed = c->s.pair_capacity > 0;
   Timer t(c, SIXDGS_K_SORT, st);
-  launch_bin_count(c->sb, prepped, st);
+  launch_bin_count(c->sb, c->vt, prepped, st);
   int64_t hint = c->sb.pcap;
   bool regrown = false;
   if (!fixed) {
     // read the pair count back, then size the pair buffers exactly (with slack for the next call)
-    if (hipMemcpyAsync(c->host_counters, c->counters.p, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, st) !=
+    if (hipMemcpyAsync(c->host_counters, c->counters.p, kCounters * sizeof(uint32_t), hipMemcpyDeviceToHost, st) !=
             hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
       return fail(c, SIXDGS_ERR_HIP, "pair count read-back failed");
@@ -439,7 +444,7 @@ sixdgs_status run_binning(sixdgs_ctx* c, int64_t E, bool prepped, hipStream_t st
       fill_sort_buffers(c, E);  // keeps dsorted: the depth-sorted entries are untouched
       regrown = true;
     }
-    hint = P;
+    hint = c->host_counters[7];
   }
   launch_bin_emit(c->sb, c->vt, hint, regrown, st);
   return check_launch(c, "binning");
@@ -474,8 +479,16 @@ bool read_back(std::vector<T>& h, const T* d, int64_t count) {
   return count <= 0 || hipMemcpy(h.data(), d, (size_t)count * sizeof(T), hipMemcpyDeviceToHost) == hipSuccess;
 }
 
-// The invariants of the last binning (sixdgs_debug_check_bins on host copies
-// of its outputs); with `items`, also the backward's work items and each
+// The tile id of each of P pairs, from the tiles' ranges.
+std::vector<uint32_t> pair_tiles(const std::vector<uint32_t>& ranges, int64_t T, int64_t P) {
+  std::vector<uint32_t> keys((size_t)std::max<int64_t>(P, 0), 0u);
+  for (int64_t t = 0; t < T; t++)
+    for (int64_t i = ranges[2 * t]; i < std::min<int64_t>(ranges[2 * t + 1], P); i++) keys[i] = (uint32_t)t;
+  return keys;
+}
+
+// The invariants of the last binning (each pair's tile in its entry's tile
+// rectangle, and sixdgs_debug_check_bins on host copies of its outputs); with `items`, also the backward's work items and each
 // pixel's last contributor and final transmittance against its tile.  "" if
 // they hold.
 std::string debug_check_binning(sixdgs_ctx* c, const float* depth_dev, bool items) {
@@ -483,14 +496,28 @@ std::string debug_check_binning(sixdgs_ctx* c, const float* depth_dev, bool item
   if (hipMemcpy(cnt, c->counters.p, sizeof(cnt), hipMemcpyDeviceToHost) != hipSuccess) return "counter read-back failed";
   const int64_t E = c->sb.E, P = cnt[1], T = c->vt.total_tiles;
   if (P > c->sb.pcap) return "";  // overflow of the fixed capacity: no output to check (sixdgs_check reports it)
-  std::vector<uint32_t> tiles, keys, vals, ranges, order, nch, its;
+  std::vector<uint32_t> tiles, vals, ranges, order, nch, its;
   std::vector<float> depth;
+  std::vector<Rec> rec;
   if (!read_back(tiles, c->tiles.p, E) || !read_back(depth, depth_dev, E) ||
-      !read_back(keys, (const uint32_t*)c->sb.pkey[c->sb.psorted], P) ||
+      !read_back(rec, (const Rec*)c->rec.p, E) ||
       !read_back(vals, (const uint32_t*)c->sb.pval[c->sb.psorted], P) ||
       !read_back(ranges, (const uint32_t*)c->ranges.p, 2 * T) || !read_back(order, (const uint32_t*)c->tile_order.p, T))
     return "binning read-back failed";
   if ((int64_t)cnt[0] > E) return "binned entries " + std::to_string(cnt[0]) + " > " + std::to_string(E);
+  const std::vector<uint32_t> keys = pair_tiles(ranges, T, P);
+  for (int64_t i = 0; i < P; i++) {
+    const uint32_t t = keys[i], e = vals[i];
+    if ((int64_t)e >= E) return "pair " + std::to_string(i) + ": entry id " + std::to_string(e) + " >= " + std::to_string(E);
+    const ViewDesc& vd = c->vt.v[e / c->vt.n];
+    const Rec& r = rec[e];
+    auto cell = [](float x, int shift) { return (int)std::fmin(std::fmax(std::floor(x / (float)(1 << shift)), -2e9f), 2e9f); };
+    const int sx = c->vt.tile_shift_x, sy = c->vt.tile_shift_y;
+    const int local = (int)t - vd.tile_base, x = local % vd.ntx, y = local / vd.ntx;
+    if (local < 0 || y >= vd.nty || x < cell(r.a.x - r.b.z, sx) || x > cell(r.a.x + r.b.z, sx) ||
+        y < cell(r.a.y - r.b.w, sy) || y > cell(r.a.y + r.b.w, sy))
+      return "pair " + std::to_string(i) + ": tile " + std::to_string(t) + " is not one of entry " + std::to_string(e);
+  }
   sixdgs_bin_state b{};
   b.E = E;
   b.P = P;
@@ -594,7 +621,7 @@ sixdgs_status sixdgs_create(sixdgs_ctx** out, const sixdgs_settings* s) {
   sixdgs_ctx* c = new (std::nothrow) sixdgs_ctx();
   if (!c) return SIXDGS_ERR_OOM;
   c->s = *s;
-  if (hipHostMalloc((void**)&c->host_counters, 4 * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void**)&c->host_counters, kCounters * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
     delete c;
     return SIXDGS_ERR_HIP;
   }
@@ -1156,12 +1183,12 @@ sixdgs_status sixdgs_export(sixdgs_ctx* c, int32_t what, void* dst, int64_t cap_
       return copy(c->counts.p, c->fwd_px * 4);
     case SIXDGS_EXPORT_KEYS: {
       if (P * 8 > cap_bytes) return fail(c, SIXDGS_ERR_INVALID_ARG, "destination too small");
-      std::vector<uint32_t> tk(P), tv(P);
-      std::vector<Rec> rec(E);
-      if ((P && (hipMemcpy(tk.data(), c->sb.pkey[c->sb.psorted], P * 4, hipMemcpyDeviceToHost) != hipSuccess ||
-                 hipMemcpy(tv.data(), c->sb.pval[c->sb.psorted], P * 4, hipMemcpyDeviceToHost) != hipSuccess)) ||
-          (E && hipMemcpy(rec.data(), c->rec.p, E * sizeof(Rec), hipMemcpyDeviceToHost) != hipSuccess))
+      std::vector<uint32_t> tv, ranges;
+      std::vector<Rec> rec;
+      if (!read_back(tv, (const uint32_t*)c->sb.pval[c->sb.psorted], P) || !read_back(rec, (const Rec*)c->rec.p, E) ||
+          !read_back(ranges, (const uint32_t*)c->ranges.p, 2 * T))
         return fail(c, SIXDGS_ERR_HIP, "read-back failed");
+      const std::vector<uint32_t> tk = pair_tiles(ranges, T, P);
       uint64_t* o = (uint64_t*)dst;
       for (int64_t i = 0; i < P; i++) {
         uint32_t bits;

@@ -33,7 +33,7 @@ struct ViewDesc {
   int32_t W, H;
   int32_t ntx, nty;   // tiles per row / column
   int32_t tile_base;  // first global tile id of this view
-  int32_t pad0;
+  int32_t patch_base; // first global patch (8 x 8 tiles) id of this view
   int64_t pix_base;   // offset of this view in the per-pixel state arrays
   float* img;         // [3][H][W] output (forward)
   const float* dimg;  // [3][H][W] upstream gradient (backward)
@@ -45,7 +45,7 @@ struct ViewTable {
   int32_t nview;
   int32_t tile_w, tile_h;
   int32_t tile_shift_x, tile_shift_y;  // log2 of tile_w, tile_h
-  int32_t total_tiles;
+  int32_t total_tiles, total_patches;
   int64_t n;  // Gaussians (entry e = view * n + gaussian)
   ViewDesc v[kMaxViews];
 };
@@ -172,44 +172,50 @@ struct SortBuffers {
   uint32_t* tiles;      // [E] tiles touched (input)
   const Rec* rec;       // [E]
   const float* depth;   // [E] camera depth of every binned entry
-  uint32_t* dkey[2];    // [E] depth keys (ping-pong)
+  uint32_t* dkey[2];    // [E] depth keys (ping-pong); after the depth sort the sorted entries' rectangles
   uint32_t* dval[2];    // [E] entry ids
-  uint32_t* poff;       // [E] exclusive pair offsets of the depth-sorted entries
+  uint32_t* poff;       // [E] exclusive item offsets of the depth-sorted entries (one per patch that an entry touches)
   // pairs
   int64_t pcap;
-  uint32_t* pkey[2];    // [pcap] global tile ids
+  uint32_t* pkey[2];    // [pcap] keys of the items' sort: patch ids with the covered tiles
   uint32_t* pval[2];    // [pcap] entry ids
   uint2* ranges;        // [total_tiles]
   // scratch
   uint32_t* rstate_depth;  // [sort_state_words(E, false)] state of the scans and the depth sort
-  uint32_t* rstate_pairs;  // [sort_state_words(pcap, true)] radix state of the tile sort
+  uint32_t* rstate_pairs;  // [sort_state_words(pcap, true) + list_state_words(..)] state of the items' sort and the lists
   uint32_t* blk_start;     // [nblk_start] first sorted entry of each emission block
   int64_t nblk_start;      // sort_block_starts(pcap) when the pair buffers were sized
   int64_t total_tiles;     // tiles of the views being binned
+  int64_t total_patches;   // patches of 8 x 8 tiles
   uint32_t* tile_order;    // [total_tiles] tiles, longest lists first (the compositing order)
   float* g2d;              // [E][kG2D] screen-space gradient accumulators to clear, or nullptr
   uint32_t* order_state;   // [order_state_words()] bucket counts and cursors of the tile order
   uint32_t* n_items;       // the backward work-item count, zeroed here and counted by the forward
-  uint32_t* counters;      // [0] binned entries, [1] pairs, [2] overflow flag, [3] sort look-back timeout
+  uint32_t* counters;      // [0] binned entries, [1] pairs, [2] overflow flag, [3] sort look-back timeout, [7] sorted items
   // where the sorted results ended up (index into the ping-pong pairs)
-  int dsorted, psorted;
+  int dsorted;
+  int psorted;  // pval[psorted] holds the pairs' entries
 };
 // Scratch sizes (32-bit words) of the integer stage for a bound on the items.
 int64_t sort_state_words(int64_t bound, bool pairs);
+int64_t list_state_words(int64_t E, int64_t total_tiles, int64_t total_patches);
 int64_t sort_block_starts(int64_t pcap);
 int64_t order_state_words();
-// Stage 1: compaction of binned entries and their depth sort, then the pair
-// offsets; leaves counters[0] = binned entries, counters[1] = pairs.
 // The preparation of the integer stage over b (for launch_preprocess).
 BinPrep bin_prep(const SortBuffers& b);
+// Stage 1: compaction of binned entries and their depth sort, then their
+// rectangles and, where the lists are built from sorted items, the item
+// offsets; leaves counters[0] = binned entries, counters[1] = pairs and
+// counters[7] = sorted items (0 where there are none).
 // prepped: bin_prep(b) has been done by an earlier launch on the stream.
-void launch_bin_count(SortBuffers& b, bool prepped, hipStream_t st);
-// Stage 2: emission of (tile, entry) pairs, their stable tile sort and the
-// per-tile ranges; `pairs_hint` bounds the launch sizes (the capacity in
-// fixed mode, the exact count otherwise).  `regrown`: the pair buffers and
-// the scratch were reallocated after stage 1, so the pair sort's histograms
-// and the emission blocks' first entries are set up again.
-void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t pairs_hint, bool regrown, hipStream_t st);
+void launch_bin_count(SortBuffers& b, const ViewTable& vt, bool prepped, hipStream_t st);
+// Stage 2: the (tile, entry) pairs' entries in (tile, depth) order and the
+// per-tile ranges; `items_hint` bounds the sorted items and with them the
+// launch sizes (the capacity in fixed mode, the exact count otherwise).
+// `regrown`: the pair buffers and the scratch were reallocated after stage 1,
+// so the sort's histograms and the emission blocks' first entries are set up
+// again.
+void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t items_hint, bool regrown, hipStream_t st);
 // Zero the screen-space gradient accumulators of the binned entries.
 void launch_zero_g2d(const SortBuffers& b, float* g2d, hipStream_t st);
 // sixdgs_bin's record import: (u, v, ex, ey, depth, alive) -> Rec + tiles.

@@ -1,10 +1,12 @@
 // Integer stage of the rasteriser on gfx950: compaction of the binned entries,
-// an LSD radix sort of their float32 depths, emission of one (tile, entry) pair
-// per covered tile in depth order, a stable LSD radix sort of the pairs by
-// global tile id and the per-tile [start, end) ranges.  Sorting depth before
-// duplication makes the two-key (tile, depth) order cost 4 passes over the
-// binned entries plus ceil(tile bits / 8) passes over the pairs, instead of a
-// 64-bit sort of the pairs.
+// an LSD radix sort of their float32 depths, and the tiles' lists -- for every
+// tile the entries that touch it, in depth order -- with their [start, end)
+// ranges.  The (tile, entry) pairs are never sorted: a wavefront takes 64
+// depth-ordered entries and a patch of 8 x 8 tiles, and ballots of the columns
+// and rows that the entries cover give each tile its entries, so a pair costs
+// one write.  Which entries touch a patch is found by testing them all where
+// that is cheap; otherwise each entry is emitted once per patch it touches
+// (about a twelfth of the pairs) and these items are radix sorted by patch.
 //
 // Every kernel reads its element count from device memory and takes a grid
 // sized by a host-side upper bound, so the stage needs no host round trip
@@ -68,11 +70,10 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t& total)
 constexpr int kRItems = 16;
 constexpr int kRItemsSmall = 8;           // short sorts: 2048 items per workgroup, 2x the workgroups
 constexpr int64_t kLargeSort = 1 << 20;    // from this many entries the depth sort uses kRItems
-constexpr int64_t kLargePairs = 1 << 24;   // from this pair capacity on the pair sort uses kRItems
-// Items per thread of the pair sort's workgroups (and pairs per emission
-// block: kBlock times this).  Measured: 2,048-pair blocks 5 us faster on one
-// 800x800 view (3.2M pairs), 4,096 6% faster on eight 1080p views.
-inline int pair_items(int64_t pcap) { return pcap >= kLargePairs ? kRItems : kRItemsSmall; }
+constexpr int64_t kLargePairs = 1 << 27;   // from this pair capacity on the items' sort uses kRItems
+// Items per thread of the item sort's workgroups (and items per emission
+// block: kBlock times this); a dozen pairs are an item.
+inline int sort_items(int64_t pcap) { return pcap >= kLargePairs ? kRItems : kRItemsSmall; }
 constexpr uint32_t kStAgg = 1u << 30;
 constexpr uint32_t kStIncl = 2u << 30;
 constexpr uint32_t kStVal = kStAgg - 1u;
@@ -116,14 +117,15 @@ inline int64_t radix_blocks(int64_t bound, int items) {
   return (bound + chunk - 1) / chunk;
 }
 
-RadixState radix_state(uint32_t* base, int64_t bound, int items, bool with_scans) {
+// extra: words between the tickets and the status words.
+RadixState radix_state(uint32_t* base, int64_t bound, int items, bool with_scans, int64_t extra = 0) {
   RadixState r;
   r.items = items;
   r.nblk = radix_blocks(bound, items);
   r.nscan = with_scans ? (bound + kChunk - 1) / kChunk : 0;
   r.ghist = base;
   r.tickets = base + kGhCopies * kGhStride;
-  r.status = base + (kGhCopies + 1) * kGhStride;
+  r.status = base + (kGhCopies + 1) * kGhStride + extra;
   r.scan_status = reinterpret_cast<uint64_t*>(r.status + (int64_t)kMaxPasses * r.nblk * 256);
   return r;
 }
@@ -201,6 +203,8 @@ __device__ uint32_t look_back(const W* status, int64_t stride, int64_t blk, uint
   return excl;
 }
 
+constexpr int kPsum = 16, kPsumStride = 32;  // words of one sum, a cache line apart
+
 // Single-pass exclusive scan of f(i) over i < count, handing (i, prefix,
 // value) to g.  Workgroups take 2048 items each in ticket order and chain
 // their prefixes through look-back words; the workgroup holding the last item
@@ -209,7 +213,7 @@ __device__ uint32_t look_back(const W* status, int64_t stride, int64_t blk, uint
 template <class F, class G, bool HIST>
 __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap,
                                                   uint32_t* ticket, uint64_t* status, uint32_t* total_out,
-                                                  uint32_t* ghist, uint32_t* err) {
+                                                  uint32_t* ghist, uint32_t* psum, uint32_t* err) {
   __shared__ uint32_t s_blk, s_pre;
   __shared__ uint32_t s_h[HIST ? kMaxPasses : 1][256];
   const int t = threadIdx.x;
@@ -233,6 +237,17 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
   for (int k = 0; k < kItems; k++) {
     v[k] = (base + k < count) ? f(base + k) : 0u;
     sum += v[k];
+  }
+  if constexpr (HIST) {
+    uint32_t all;
+    block_scan_excl(sum, all);
+    if (t == 0 && all) atomicAdd(&psum[blk % kPsum * kPsumStride], all);
+    sum = 0;
+#pragma unroll
+    for (int k = 0; k < kItems; k++) {
+      v[k] = v[k] ? 1u : 0u;
+      sum += v[k];
+    }
   }
   uint32_t total;
   uint32_t pre = block_scan_excl(sum, total);
@@ -276,11 +291,11 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
 
 template <bool HIST, class F, class G>
 void scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap, int64_t bound, uint32_t* ticket,
-           uint64_t* status, uint32_t* total_out, uint32_t* ghist, uint32_t* err, hipStream_t st) {
+           uint64_t* status, uint32_t* total_out, uint32_t* ghist, uint32_t* psum, uint32_t* err, hipStream_t st) {
   int64_t nb = (bound + kChunk - 1) / kChunk;
   if (nb < 1) nb = 1;  // one workgroup writes a zero total
   hipLaunchKernelGGL((k_scan1<F, G, HIST>), dim3((unsigned)nb), dim3(kBlock), 0, st, f, g, count_ptr, fixed, cap,
-                     ticket, status, total_out, ghist, err);
+                     ticket, status, total_out, ghist, psum, err);
 }
 
 // Up to four word ranges a preparation kernel zeroes.
@@ -297,8 +312,7 @@ struct ZeroList {
 __global__ void __launch_bounds__(kBlock) k_stage_prep(RadixState rs, int64_t zero_words, ZeroList z,
                                                        uint2* __restrict__ ranges, int64_t nranges,
                                                        const uint32_t* __restrict__ counters,
-                                                       const uint32_t* __restrict__ tiles,
-                                                       const uint32_t* __restrict__ dval,
+                                                       const uint32_t* __restrict__ total,
                                                        const uint32_t* __restrict__ poff, uint32_t pcap,
                                                        uint32_t* __restrict__ blk_start, int64_t nblk_start,
                                                        uint32_t chunk) {
@@ -310,7 +324,7 @@ __global__ void __launch_bounds__(kBlock) k_stage_prep(RadixState rs, int64_t ze
   if (ranges && i < nranges) ranges[i] = make_uint2(0xFFFFFFFFu, 0u);  // merged by min / max
   if (blk_start && i < (int64_t)counters[0] && counters[1] <= pcap) {
     const uint32_t o = poff[i];
-    const uint32_t end = o + tiles[dval[i]];
+    const uint32_t end = i + 1 < (int64_t)counters[0] ? poff[i + 1] : *total;
     for (uint32_t b = (o + chunk - 1) / chunk; (int64_t)b * chunk < end && b < nblk_start; b++)
       blk_start[b] = (uint32_t)i;
   }
@@ -538,9 +552,7 @@ __global__ void __launch_bounds__(kBlock) k_digit_scatter(const uint32_t* __rest
                                                           const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
                                                           uint32_t* __restrict__ vout, const uint32_t* count_ptr,
                                                           uint32_t cap, int shift, int dbits,
-                                                          const uint32_t* __restrict__ table, int64_t nblk,
-                                                          uint2* __restrict__ ranges, uint32_t total_tiles,
-                                                          const uint32_t* __restrict__ counters, uint32_t pcap) {
+                                                          const uint32_t* __restrict__ table, int64_t nblk) {
   constexpr int kChunkI = kBlock * ITEMS;
   __shared__ uint32_t s_key[kChunkI];
   __shared__ uint32_t s_val[kChunkI];
@@ -586,13 +598,6 @@ __global__ void __launch_bounds__(kBlock) k_digit_scatter(const uint32_t* __rest
   __syncthreads();
   const int64_t left = (int64_t)count - base;
   const int nvalid = left < kChunkI ? (int)left : kChunkI;
-  // the last pass also finds the tiles' ranges: the workgroup's digit runs
-  // are sorted by the whole key, so where the key changes inside a run is
-  // where the output changes key; a run's ends meet other workgroups' items,
-  // so every end is merged with a device min / max (ranges start at
-  // (UINT_MAX, 0); the tile order turns the untouched ones into (0, 0)).
-  // Skipped when the pairs overflowed: every range then stays empty.
-  const bool with_ranges = ranges && counters[1] <= pcap;
 #pragma unroll
   for (int r = 0; r < ITEMS; r++) {
     const int k = r * kBlock + t;
@@ -602,10 +607,6 @@ __global__ void __launch_bounds__(kBlock) k_digit_scatter(const uint32_t* __rest
       if (o < count) {  // always true for consistent tables; guards the buffers
         kout[o] = kk;
         vout[o] = s_val[k];
-        if (with_ranges && kk < total_tiles) {
-          if (k == 0 || s_key[k - 1] != kk) atomicMin(&ranges[kk].x, o);
-          if (k == nvalid - 1 || s_key[k + 1] != kk) atomicMax(&ranges[kk].y, o + 1u);
-        }
       }
     }
   }
@@ -630,9 +631,9 @@ int radix_sort(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* count_ptr, 
 }
 
 // ------------------------------------------------------------ the stage
-struct BinnedFlag {
+struct TileCount {
   const uint32_t* tiles;
-  __device__ uint32_t operator()(int64_t i) const { return tiles[i] > 0 ? 1u : 0u; }
+  __device__ uint32_t operator()(int64_t i) const { return tiles[i]; }
 };
 struct CompactDepth {
   const float* depth;
@@ -647,18 +648,66 @@ struct CompactDepth {
     }
   }
 };
-struct SortedTiles {
-  const uint32_t* tiles;
-  const uint32_t* dval;
-  __device__ uint32_t operator()(int64_t i) const { return tiles[dval[i]]; }
+// The tile rectangle of a sorted entry: x first | x last << 11 | view << 22,
+// and y first | y last << 11 (a view has at most 2,048 tiles each way); an
+// empty one is in no patch.
+__device__ __forceinline__ uint2 entry_rect(const ViewTable& vt, const Rec* rec, uint32_t e) {
+  const uint32_t view = e / (uint32_t)vt.n;
+  const ViewDesc& vd = vt.v[view];
+  const float4 ra = rec[e].a, rb = rec[e].b;
+  int x0, y0, x1, y1;
+  tile_rect(ra.x, ra.y, rb.z, rb.w, vt.tile_shift_x, vt.tile_shift_y, vd.ntx, vd.nty, x0, y0, x1, y1);
+  if (x1 <= x0 || y1 <= y0) return make_uint2(2047u, 2047u);  // x last = y last = 0: before the first
+  return make_uint2((uint32_t)(x0 | (x1 - 1) << 11) | view << 22, (uint32_t)(y0 | (y1 - 1) << 11));
+}
+
+// All sorted entries' rectangles, and the pair count from its partial sums.
+__global__ void __launch_bounds__(kBlock) k_rects(ViewTable vt, const Rec* __restrict__ rec,
+                                                  const uint32_t* __restrict__ dval, const uint32_t* __restrict__ psum,
+                                                  uint32_t* __restrict__ counters, uint32_t* __restrict__ rect0,
+                                                  uint32_t* __restrict__ rect1) {
+  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    const uint32_t s = wave_scan_incl(threadIdx.x < kPsum ? psum[threadIdx.x * kPsumStride] : 0u);
+    if (threadIdx.x == 63) {
+      counters[1] = s;
+      counters[7] = 0u;
+    }
+  }
+  if (i >= counters[0]) return;
+  const uint2 r = entry_rect(vt, rec, dval[i]);
+  rect0[i] = r.x;
+  rect1[i] = r.y;
+}
+
+// The patches that a sorted entry's rectangle touches.
+struct PatchCount {
+  const uint32_t* rect0;
+  const uint32_t* rect1;
+  __device__ uint32_t operator()(int64_t i) const {
+    const uint32_t x = rect0[i], y = rect1[i];
+    const int w = (int)((x >> 14) & 255u) - (int)((x >> 3) & 255u) + 1;
+    const int h = (int)((y >> 14) & 255u) - (int)((y >> 3) & 255u) + 1;
+    return w > 0 && h > 0 ? (uint32_t)(w * h) : 0u;
+  }
 };
-// The pair offset of each depth-sorted entry, and for every emission block
-// that starts inside the entry's pairs, the entry.
+struct CountVal {
+  const uint32_t* c;
+  __device__ uint32_t operator()(int64_t i) const { return c[i]; }
+};
+struct StoreRange {
+  uint2* ranges;
+  __device__ void operator()(int64_t i, uint32_t pre, uint32_t n) const {
+    ranges[i] = n ? make_uint2(pre, pre + n) : make_uint2(0u, 0u);
+  }
+};
+// The item offset of each depth-sorted entry, and for every emission block
+// that starts inside the entry's items, the entry.
 struct StoreOffset {
   uint32_t* poff;
   uint32_t* blk_start;
   int64_t nblk_start;
-  int64_t chunk;  // pairs per emission block
+  int64_t chunk;  // items per emission block
   __device__ void operator()(int64_t i, uint32_t pre, uint32_t n) const {
     poff[i] = pre;
     for (int64_t b = ((int64_t)pre + chunk - 1) / chunk; b * chunk < (int64_t)pre + n && b < nblk_start; b++)
@@ -666,40 +715,48 @@ struct StoreOffset {
   }
 };
 
-// Load-balanced pair emission: workgroup b writes pairs [chunk b, chunk (b + 1))
-// in depth order.  It walks the depth-sorted entries from the one holding its
-// first pair, 256 entries per step; each thread finds the entry of a pair by
-// binary search over the entries' pair offsets in LDS and the pair's tile from
-// its index in the entry's tile rectangle (row-major, the order the count
-// came from), so consecutive threads write consecutive pairs whatever the
-// entries' sizes.  The digit histograms of every pass of the tile sort are
-// accumulated on the way.
-__global__ void __launch_bounds__(kBlock) k_emit(ViewTable vt, const Rec* __restrict__ rec,
+// whether the call's pairs did not fit (no list is written then)
+__device__ __forceinline__ bool overflowed(const uint32_t* counters, uint32_t pcap) {
+  return max(counters[1], counters[7]) > pcap;
+}
+
+// Load-balanced emission of the (patch, entry) items: workgroup b writes items
+// [chunk b, chunk (b + 1)) in depth order.  It walks the depth-sorted entries
+// from the one holding its first item, 256 entries per step; each thread finds
+// the entry of an item by binary search over the entries' item offsets in LDS
+// and the item's patch from its index in the entry's rectangle of patches
+// (row-major, the order the count came from), so consecutive threads write
+// consecutive items whatever the entries' sizes.  The digit histograms of every
+// pass of the sort are accumulated on the way.  An item's key: the patch's id,
+// and above its 20 bits the tiles of the patch that the entry covers (x first,
+// x last, y first, y last, 3 bits each).
+constexpr uint32_t kPatchMask = (1u << 20) - 1u;
+
+__global__ void __launch_bounds__(kBlock) k_emit(ViewTable vt, const uint32_t* __restrict__ rect0,
+                                                 const uint32_t* __restrict__ rect1,
                                                  const uint32_t* __restrict__ dval, const uint32_t* __restrict__ poff,
                                                  const uint32_t* __restrict__ blk_start,
                                                  uint32_t* __restrict__ counters, uint32_t pcap, int npass, int dbits,
                                                  uint32_t* __restrict__ ghist, uint32_t* __restrict__ pkey,
                                                  uint32_t* __restrict__ pval, uint32_t* __restrict__ table0,
                                                  uint32_t chunk) {
-  __shared__ uint32_t s_o[kBlock + 1];  // pair offset of each entry of the step; [kBlock]: the next step's
+  __shared__ uint32_t s_o[kBlock + 1];  // item offset of each entry of the step; [kBlock]: the next step's
   __shared__ uint32_t s_e[kBlock];      // entry id
-  __shared__ uint32_t s_base[kBlock];   // global id of the rectangle's first tile
-  __shared__ uint32_t s_w[kBlock];      // rectangle width in tiles
-  __shared__ uint32_t s_ntx[kBlock];    // tiles per row of the entry's view
+  __shared__ uint32_t s_x[kBlock], s_y[kBlock];  // its rectangle
   __shared__ uint32_t s_h[kMaxPasses][256];
   const int t = threadIdx.x;
   // blk_start holds an entry for every workgroup of the grid: read with the
   // counts, not after them
   uint32_t ib = blk_start[blockIdx.x];
   const uint32_t nb = counters[0];
-  const uint32_t P = counters[1];
-  if (P > pcap) {
+  const uint32_t S = counters[7];
+  if (overflowed(counters, pcap)) {
     if (blockIdx.x == 0 && t == 0) counters[2] = 1u;
     return;
   }
   const int64_t p0 = (int64_t)blockIdx.x * chunk;
-  if (p0 >= P) return;  // uniform
-  const uint32_t p1 = (uint32_t)min<int64_t>(p0 + chunk, (int64_t)P);
+  if (p0 >= S) return;  // uniform
+  const uint32_t p1 = (uint32_t)min<int64_t>(p0 + chunk, (int64_t)S);
   const uint32_t mask = (1u << dbits) - 1u;
 #pragma unroll
   for (int p = 0; p < kMaxPasses; p++) s_h[p][t] = 0;
@@ -708,40 +765,37 @@ __global__ void __launch_bounds__(kBlock) k_emit(ViewTable vt, const Rec* __rest
     if (i < nb) {
       const uint32_t o = poff[i];
       s_o[t] = o;
-      // an entry whose pairs start past this block is never chosen by the
-      // search below: its record is not read (a block of 2,048 pairs needs
-      // about a hundred of the step's entries)
+      // an entry whose items start past this block is never chosen by the
+      // search below: its rectangle is not read
       if (o < p1) {
-        const uint32_t e = dval[i];
-        const ViewDesc& vd = vt.v[e / (uint64_t)vt.n];
-        const float4 ra = rec[e].a, rb = rec[e].b;
-        int x0, y0, x1, y1;
-        tile_rect(ra.x, ra.y, rb.z, rb.w, vt.tile_shift_x, vt.tile_shift_y, vd.ntx, vd.nty, x0, y0, x1, y1);
-        s_e[t] = e;
-        s_base[t] = (uint32_t)(vd.tile_base + y0 * vd.ntx + x0);
-        s_w[t] = (uint32_t)(x1 - x0);
-        s_ntx[t] = (uint32_t)vd.ntx;
+        s_e[t] = dval[i];
+        s_x[t] = rect0[i];
+        s_y[t] = rect1[i];
       }
     } else {
-      s_o[t] = P;  // past the last entry: never chosen by the search below
+      s_o[t] = S;  // past the last entry: never chosen by the search below
     }
-    if (t == 0) s_o[kBlock] = (uint64_t)ib + kBlock < nb ? poff[ib + kBlock] : P;
+    if (t == 0) s_o[kBlock] = (uint64_t)ib + kBlock < nb ? poff[ib + kBlock] : S;
     __syncthreads();
     const uint32_t lo = max((uint32_t)p0, s_o[0]);
     const uint32_t hi = min(p1, s_o[kBlock]);
     for (uint32_t q = lo + t; q < hi; q += kBlock) {
-      int j = 0;  // last entry of the step whose pairs start at or before q
+      int j = 0;  // last entry of the step whose items start at or before q
 #pragma unroll
       for (int step = kBlock / 2; step > 0; step >>= 1)
         if (s_o[j + step] <= q) j += step;
       const uint32_t local = q - s_o[j];
-      const uint32_t w = s_w[j];
-      const uint32_t ty = local / w;
-      const uint32_t key = s_base[j] + ty * s_ntx[j] + (local - ty * w);
+      const uint32_t rx = s_x[j], ry = s_y[j];
+      const uint32_t px0 = (rx >> 3) & 255u, px1 = (rx >> 14) & 255u, py0 = (ry >> 3) & 255u, py1 = (ry >> 14) & 255u;
+      const uint32_t w = px1 - px0 + 1;
+      const uint32_t ty = local / w, px = px0 + (local - ty * w), py = py0 + ty;
+      const uint32_t tiles = (px == px0 ? rx & 7u : 0u) | (px == px1 ? (rx >> 11) & 7u : 7u) << 3 |
+                             (py == py0 ? ry & 7u : 0u) << 6 | (py == py1 ? (ry >> 11) & 7u : 7u) << 9;
+      const ViewDesc& vd = vt.v[rx >> 22];
+      const uint32_t key = tiles << 20 | (vd.patch_base + py * ((vd.ntx + 7) >> 3) + px);
       pkey[q] = key;
       pval[q] = s_e[j];
-      // Lanes whose digit equals the first active lane's add as one: the
-      // tiles of one wide Gaussian share their high digits, and same-address
+      // Lanes whose digit equals the first active lane's add as one: same-address
       // shared-memory atomics from one wavefront serialise.
       const uint64_t act = __ballot(1);
       const bool leader = __lane_id() == (unsigned)(__ffsll((unsigned long long)act) - 1);
@@ -771,33 +825,40 @@ __global__ void __launch_bounds__(kBlock) k_emit(ViewTable vt, const Rec* __rest
 // (buckets of log2 of the pair count, heaviest bucket first), so the tiles
 // whose per-pixel walks are longest start before the light ones and the
 // kernels' tails shrink (LPT scheduling); the order inside a bucket is
-// arbitrary.  Up to kOrderOneGroup tiles one workgroup of 1024 threads takes
-// the bucket histogram, its scan and the scatter; beyond, k_order_count and
-// k_order_place split the same over many workgroups, which reserve their
-// places inside each bucket with one device atomic per bucket.  Workgroups
-// past the ordering ones zero the screen-space gradient accumulators of the
-// binned entries (when g2d is given) for the backward that may follow.
-constexpr int kOrderThreads = 1024;
+// arbitrary.  k_list_scan counts the buckets, into kOrderCopies copies by
+// patch; workgroups of the kernel that writes the lists then take
+// kOrderTiles tiles each, reserve their places inside each bucket with one
+// device atomic per bucket and write the order beside the others' lists.
 constexpr int kOrderBuckets = 33;
-constexpr int kOrderU = 8;                                   // tiles per thread and round
-constexpr uint32_t kOrderGroupTiles = kOrderThreads * kOrderU;
-constexpr uint32_t kOrderOneGroup = 2 * kOrderGroupTiles;    // one workgroup orders up to this many tiles
-constexpr int kOrderStateWords = 2 * kOrderBuckets;          // bucket counts, then bucket cursors
+constexpr int kOrderU = 4;                                  // tiles per thread
+constexpr uint32_t kOrderTiles = kBlock * kOrderU;
+constexpr int kOrderCopies = 16;
+constexpr int kOrderStateWords = 64 * (kOrderCopies + 1);   // bucket counts, then bucket cursors
 
-// the bucket of tile k (heaviest first: slot 0 holds 2^31 pairs and more, the
-// last slot the empty tiles), -1 past the last tile
-// FIX: also turn a range the sort left untouched ((UINT_MAX, 0): a tile
-// without pairs) into (0, 0), the form every later reader expects.
-template <bool FIX>
-__device__ __forceinline__ int order_slot(uint2* __restrict__ ranges, uint32_t total_tiles, uint32_t k) {
-  if (k >= total_tiles) return -1;
-  const uint2 r = ranges[k];
-  uint32_t c = r.y - r.x;
-  if (r.x >= r.y) {
-    c = 0;
-    if (FIX && (r.x | r.y)) ranges[k] = make_uint2(0u, 0u);
+__host__ __device__ inline uint32_t order_wgs(uint32_t total_tiles) { return (total_tiles + kOrderTiles - 1) / kOrderTiles; }
+
+// the bucket of a tile with c pairs (heaviest first: 0 holds 2^31 pairs and
+// more, the last the empty tiles)
+__device__ __forceinline__ int order_bucket(uint32_t c) { return kOrderBuckets - 1 - (c ? 32 - __clz(c) : 0); }
+
+// A wavefront's lane l holds a counter of bucket l.  Per lane with b >= 0, adds
+// one to bucket b's; returns what it was before for the first lane of a bucket,
+// one more for the next ...  In registers, since a wavefront's tiles share a few
+// buckets and shared-memory atomics on one word serialise (7,744 tiles took a
+// workgroup 11 us that way).
+__device__ __forceinline__ uint32_t bucket_add(uint32_t& n, int b) {
+  const int lane = (int)__lane_id();
+  uint32_t place = 0;
+  for (uint64_t todo = __ballot(b >= 0); todo;) {
+    const int b0 = __builtin_amdgcn_readlane(b, __ffsll((unsigned long long)todo) - 1);
+    const uint64_t same = __ballot(b == b0);
+    const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo(
+                                                                              (uint32_t)same, __builtin_amdgcn_readlane(n, b0)));
+    place = b == b0 ? at : place;
+    n += lane == b0 ? (uint32_t)__popcll(same) : 0u;
+    todo &= ~same;
   }
-  return kOrderBuckets - 1 - (c ? 32 - __clz(c) : 0);
+  return place;
 }
 
 // Zeroes the gradient-accumulator row of entry i if it is binned (a tile
@@ -813,109 +874,383 @@ __device__ __forceinline__ void zero_g2d_entry(int64_t i, const uint32_t* __rest
   }
 }
 
-// exclusive scan of the kOrderBuckets counts in s (one thread; tiny)
-__device__ __forceinline__ void scan_buckets(uint32_t* s) {
-  if (threadIdx.x == 0) {
-    uint32_t acc = 0;
-    for (int b = 0; b < kOrderBuckets; b++) {
-      const uint32_t c = s[b];
-      s[b] = acc;
-      acc += c;
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kOrderThreads) k_tile_order(uint2* __restrict__ ranges, uint32_t total_tiles,
-                                                              uint32_t* __restrict__ order,
-                                                              const uint32_t* __restrict__ tiles, int64_t E,
-                                                              float* __restrict__ g2d) {
-  __shared__ uint32_t s_h[kOrderBuckets];
-  const int t = threadIdx.x;
-  if (blockIdx.x > 0) {
-    zero_g2d_entry((int64_t)(blockIdx.x - 1) * kOrderThreads + t, tiles, E, g2d);
-    return;
-  }
-  if (t < kOrderBuckets) s_h[t] = 0;
+// The order of tiles [wg * kOrderTiles, ...), by one workgroup.
+__device__ __forceinline__ void order_tiles(const uint2* __restrict__ ranges, uint32_t total_tiles, uint32_t wg,
+                                            uint32_t* __restrict__ state, uint32_t* __restrict__ order) {
+  __shared__ uint32_t s_n[64];  // the workgroup's count per bucket, then its first place
+  const uint32_t t = threadIdx.x, lane = t & 63;
+  if (t < 64) s_n[t] = 0;
   __syncthreads();
-  const uint32_t span = (total_tiles + kOrderGroupTiles - 1) / kOrderGroupTiles * kOrderGroupTiles;
-  for (uint32_t k0 = t; k0 < span; k0 += kOrderGroupTiles) {
-    int b[kOrderU];
-#pragma unroll
-    for (int u = 0; u < kOrderU; u++) b[u] = order_slot<true>(ranges, total_tiles, k0 + u * kOrderThreads);
-#pragma unroll
-    for (int u = 0; u < kOrderU; u++)
-      if (b[u] >= 0) atomicAdd(&s_h[b[u]], 1u);
-  }
-  __syncthreads();
-  scan_buckets(s_h);
-  __syncthreads();
-  for (uint32_t k0 = t; k0 < span; k0 += kOrderGroupTiles) {
-    int b[kOrderU];
-#pragma unroll
-    for (int u = 0; u < kOrderU; u++) b[u] = order_slot<false>(ranges, total_tiles, k0 + u * kOrderThreads);
-#pragma unroll
-    for (int u = 0; u < kOrderU; u++) {
-      const uint32_t pos = b[u] >= 0 ? atomicAdd(&s_h[b[u]], 1u) : 0u;
-      if (b[u] >= 0 && pos < total_tiles) order[pos] = k0 + u * kOrderThreads;
-    }
-  }
-}
-
-// Many tiles, first half: bucket counts of kOrderGroupTiles tiles per
-// workgroup, added into state[0, kOrderBuckets) (zeroed beforehand).
-__global__ void __launch_bounds__(kOrderThreads) k_order_count(uint2* __restrict__ ranges, uint32_t total_tiles,
-                                                               uint32_t ngroups, uint32_t* __restrict__ state,
-                                                               const uint32_t* __restrict__ tiles, int64_t E,
-                                                               float* __restrict__ g2d) {
-  __shared__ uint32_t s_h[kOrderBuckets];
-  const int t = threadIdx.x;
-  if (blockIdx.x >= ngroups) {
-    zero_g2d_entry((int64_t)(blockIdx.x - ngroups) * kOrderThreads + t, tiles, E, g2d);
-    return;
-  }
-  if (t < kOrderBuckets) s_h[t] = 0;
-  __syncthreads();
-  const uint32_t k0 = blockIdx.x * kOrderGroupTiles + t;
+  const uint32_t k0 = wg * kOrderTiles + t;
   int b[kOrderU];
-#pragma unroll
-  for (int u = 0; u < kOrderU; u++) b[u] = order_slot<true>(ranges, total_tiles, k0 + u * kOrderThreads);
-#pragma unroll
-  for (int u = 0; u < kOrderU; u++)
-    if (b[u] >= 0) atomicAdd(&s_h[b[u]], 1u);
-  __syncthreads();
-  if (t < kOrderBuckets && s_h[t]) atomicAdd(&state[t], s_h[t]);
-}
-
-// Second half: each workgroup ranks its tiles inside their buckets, reserves
-// a run of places per bucket (device atomics on state[kOrderBuckets + b]) and
-// writes the tiles there.
-__global__ void __launch_bounds__(kOrderThreads) k_order_place(uint2* __restrict__ ranges, uint32_t total_tiles,
-                                                               uint32_t* __restrict__ state,
-                                                               uint32_t* __restrict__ order) {
-  __shared__ uint32_t s_off[kOrderBuckets];   // first place of each bucket
-  __shared__ uint32_t s_loc[kOrderBuckets];   // this workgroup's count per bucket, then its reserved base
-  const int t = threadIdx.x;
-  if (t < kOrderBuckets) {
-    s_off[t] = state[t];
-    s_loc[t] = 0;
-  }
-  __syncthreads();
-  scan_buckets(s_off);
-  const uint32_t k0 = blockIdx.x * kOrderGroupTiles + t;
-  int b[kOrderU];
-  uint32_t rank[kOrderU];
-#pragma unroll
-  for (int u = 0; u < kOrderU; u++) b[u] = order_slot<false>(ranges, total_tiles, k0 + u * kOrderThreads);
-#pragma unroll
-  for (int u = 0; u < kOrderU; u++) rank[u] = b[u] >= 0 ? atomicAdd(&s_loc[b[u]], 1u) : 0u;
-  __syncthreads();
-  if (t < kOrderBuckets && s_loc[t]) s_loc[t] = atomicAdd(&state[kOrderBuckets + t], s_loc[t]);
-  __syncthreads();
 #pragma unroll
   for (int u = 0; u < kOrderU; u++) {
-    if (b[u] < 0) continue;
-    const uint32_t pos = s_off[b[u]] + s_loc[b[u]] + rank[u];
-    if (pos < total_tiles) order[pos] = k0 + u * kOrderThreads;
+    const uint32_t k = k0 + u * kBlock;
+    const uint2 r = k < total_tiles ? ranges[k] : make_uint2(0u, 0u);
+    b[u] = k < total_tiles ? order_bucket(r.y - r.x) : -1;
+  }
+  uint32_t n = 0;
+#pragma unroll
+  for (int u = 0; u < kOrderU; u++) bucket_add(n, b[u]);
+  uint32_t at = n ? atomicAdd(&s_n[lane], n) : 0u;  // the wavefront's part
+  __syncthreads();
+  if (t < 64) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < kOrderCopies; k++) c += state[64 * k + lane];
+    const uint32_t off = wave_scan_incl(c) - c;  // first place of each bucket
+    if (s_n[lane]) s_n[lane] = off + atomicAdd(&state[64 * kOrderCopies + lane], s_n[lane]);
+  }
+  __syncthreads();
+  at += s_n[lane];
+#pragma unroll
+  for (int u = 0; u < kOrderU; u++) {
+    const uint32_t pos = bucket_add(at, b[u]);
+    if (b[u] >= 0 && pos < total_tiles) order[pos] = k0 + u * kBlock;
+  }
+}
+
+// ----------------------------------------------------- the lists of the tiles
+// A wavefront takes 64 depth-ordered entries that touch a patch.  Per entry, 8
+// column and 8 row bits say which of the patch's 8 x 8 tiles it covers; the
+// ballots of the bits are, per column and row, the entries that cover it; and
+// the entries of a tile are those of its column and its row.  A first kernel
+// counts them (lane t holds tile t's) into one row of a table per chunk of
+// entries and patch; k_list_scan turns a patch's rows into exclusive prefixes and
+// its tiles' totals; the scan of the totals over the tiles gives the ranges;
+// the second kernel's lanes then know where their entries go, in each tile a
+// dozen neighbours or so at a time.  Radix sorting the pairs (8 bytes) by tile
+// moved each five times, 124 vector instructions per 64 and pass, and bound the
+// stage by memory: 16 views of 500k Gaussians, 144M pairs, 3,350 us for the
+// whole stage then and 1,080 now (342 of them the writes, 1.7 TB/s: runs of
+// 50 bytes); one 1408x1408 view of 175k, 4.9M pairs, 195 and 110; one 800x800
+// view of 300k, 3.4M pairs, 164 and 120.
+__device__ __forceinline__ uint32_t readlane(uint32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
+// lane q of (lo, hi) = m (a vector instruction may read a scalar register that
+// another wrote two wait states later)
+__device__ __forceinline__ void put_lane(uint32_t& lo, uint32_t& hi, uint64_t m, int q) {
+  asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+      : "+v"(lo), "+v"(hi)
+      : "s"((uint32_t)m), "s"((uint32_t)(m >> 32)), "n"(q));
+}
+// Has a loaded value waited for here: where it is next used, the wait would
+// also be for the stores in between (one counter holds both).
+__device__ __forceinline__ void arrived(uint32_t& v) { asm volatile("" : "+v"(v)); }
+
+// the columns and rows x0 .. x1, y0 .. y1 of a patch as 8 + 8 bits
+__device__ __forceinline__ uint32_t patch_bits(uint32_t x0, uint32_t x1, uint32_t y0, uint32_t y1) {
+  return ((2u << x1) - (1u << x0)) | ((2u << y1) - (1u << y0)) << 8;
+}
+
+// Up to 64 entries of a patch, in order by lane (bits 0: none), and its ROWS
+// rows of tiles from row0 on: lane t's n, t < 8 ROWS, moves on by the entries of
+// the t-th of these tiles, and with WRITE entry e of the lane goes to out[n ...]
+// of those it covers.  False if the output were exceeded (never for consistent
+// counts).
+template <bool WRITE, int ROWS>
+__device__ __forceinline__ bool list_entries(uint32_t bits, uint32_t e, int row0, uint32_t& n, uint32_t pcap,
+                                             uint32_t* __restrict__ out) {
+  const int lane = (int)__lane_id();
+  uint64_t col[8];
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int x = 0; x < 8; x++) {
+    col[x] = __ballot((bits >> x) & 1u);
+    put_lane(lo, hi, col[x], x);
+  }
+  const uint32_t rbits = bits >> (8 + row0);
+#pragma unroll
+  for (int r = 0; r < ROWS; r++) put_lane(lo, hi, __ballot((rbits >> r) & 1u), 8 + r);
+  const int x = lane & 7, y = 8 + ((lane >> 3) & (ROWS - 1));
+  const uint32_t cnt = (uint32_t)(__popc(__shfl(lo, x, 64) & __shfl(lo, y, 64)) +
+                                  __popc(__shfl(hi, x, 64) & __shfl(hi, y, 64)));
+  if constexpr (WRITE) {
+    if (__ballot((uint64_t)n + cnt > pcap)) return false;
+#pragma unroll 1
+    for (int r = 0; r < ROWS; r++) {
+      const uint64_t row = (uint64_t)readlane(hi, 8 + r) << 32 | readlane(lo, 8 + r);
+      if (row == 0) continue;
+#pragma unroll
+      for (int c = 0; c < 8; c++) {
+        const uint64_t m = col[c] & row;
+        const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, readlane(n, 8 * r + c)));
+        if (__builtin_amdgcn_inverse_ballot_w64(m))
+          *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(out) + (uint64_t)(uint32_t)(4 * at)) = e;
+      }
+    }
+  }
+  n += cnt;
+  return true;
+}
+
+// the view of a patch (every lane calls)
+__device__ __forceinline__ int patch_view(const ViewTable& vt, uint32_t patch) {
+  const int l = (int)__lane_id();
+  return __popcll(__ballot(l < vt.nview && (uint32_t)vt.v[min(l, kMaxViews - 1)].patch_base <= patch)) - 1;
+}
+
+// the global id of tile l of patch (px, py) of a view, or -1 past the view's edge
+__device__ __forceinline__ int patch_tile(const ViewDesc& vd, int px, int py, int l) {
+  const int x = px * 8 + (l & 7), y = py * 8 + (l >> 3);
+  return x < vd.ntx && y < vd.nty ? vd.tile_base + y * vd.ntx + x : -1;
+}
+__device__ __forceinline__ int patch_tile(const ViewTable& vt, uint32_t patch, int l) {
+  const ViewDesc& vd = vt.v[patch_view(vt, patch)];
+  const int npx = (vd.ntx + 7) >> 3, local = (int)patch - vd.patch_base, py = local / npx;
+  return patch_tile(vd, local - py * npx, py, l);
+}
+
+// Lists from the items sorted by patch, kListItems per wavefront.  Every (chunk,
+// patch) that occurs has table row chunk + patch: both only grow along the
+// items, so no two share one and a patch's are adjacent.  The first kernel also
+// writes each patch's range of the items (into `ranges`, where k_list_scan
+// reads it before the tiles' ranges go there).
+constexpr int kListSteps = 4;
+constexpr uint32_t kListItems = 64 * kListSteps;
+constexpr int kListWG = 8192;  // workgroups at most: each takes further chunks
+
+// Which unit of work a workgroup takes: consecutive ones run on different XCDs,
+// so each XCD takes a run of the units (neighbours, which complete each other's
+// cache lines).  Loops while the id is below 8 * ceil(units / 8); may return
+// an id past the last.
+__device__ __forceinline__ uint32_t xcd_unit(uint32_t b, uint32_t units) { return (b & 7u) * ((units + 7u) / 8u) + (b >> 3); }
+
+template <bool WRITE>
+__global__ void __launch_bounds__(kBlock) k_item_lists(ViewTable vt, const uint32_t* __restrict__ key,
+                                                       const uint32_t* __restrict__ val,
+                                                       const uint32_t* __restrict__ counters, uint32_t pcap,
+                                                       uint32_t* __restrict__ table, uint2* __restrict__ ranges,
+                                                       uint32_t* __restrict__ out, uint32_t* __restrict__ order_state,
+                                                       uint32_t* __restrict__ order) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t first_wg = 0;
+  if (WRITE) {  // the first workgroups order the tiles
+    first_wg = order_wgs((uint32_t)vt.total_tiles);
+    if (blockIdx.x < first_wg) {
+      order_tiles(ranges, (uint32_t)vt.total_tiles, blockIdx.x, order_state, order);
+      return;
+    }
+  }
+  if (overflowed(counters, pcap)) return;
+  const uint32_t S = counters[7];
+  const uint32_t nchunk = (S + kListItems - 1) / kListItems;
+  const uint32_t units = (nchunk + kWaves - 1) / kWaves;
+  for (uint32_t b = blockIdx.x - first_wg; b < (units + 7) / 8 * 8; b += gridDim.x - first_wg) {
+    const uint32_t u = xcd_unit(b, units);
+    const uint32_t c = u * kWaves + wv;
+    if (u >= units || c >= nchunk) continue;
+    const uint32_t i0 = c * kListItems, i1 = min(i0 + kListItems, S);
+    uint32_t patch = ~0u, n = 0;  // WRITE: where tile `lane`'s next entry goes; else its entries so far
+    if (!WRITE && i0 > 0) patch = key[i0 - 1] & kPatchMask;  // goes on from the chunk before
+    bool first = true;
+    uint32_t k = i0 + lane < i1 ? key[i0 + lane] : ~0u;
+    uint32_t e = WRITE && i0 + lane < i1 ? val[i0 + lane] : 0u;
+    for (uint32_t i = i0; i < i1; i += 64) {
+      const uint32_t in = i + 64 + lane;
+      uint32_t kn = in < i1 ? key[in] : ~0u;
+      uint32_t en = WRITE && in < i1 ? val[in] : 0u;
+      arrived(e);
+      const uint32_t id = k & kPatchMask;
+      uint64_t todo = __ballot(i + lane < i1);
+      while (todo) {
+        const int f = __ffsll((unsigned long long)todo) - 1;
+        const uint32_t p = readlane(id, f);
+        if (first || p != patch) {
+          if constexpr (WRITE) {
+            const int tile = patch_tile(vt, p, lane);
+            n = table[(uint64_t)(c + p) * 64 + lane] + (tile >= 0 ? ranges[tile].x : 0u);
+            arrived(n);
+          } else {
+            if (!first) table[(uint64_t)(c + patch) * 64 + lane] = n;
+            if (p != patch) {  // patch ends and p starts here
+              if (lane == 0) {
+                if (patch != ~0u) ranges[patch].y = i + f;
+                ranges[p].x = i + f;
+              }
+            }
+            n = 0;
+          }
+          patch = p;
+          first = false;
+        }
+        todo &= ~__ballot(id == p);
+        const uint32_t r = k >> 20;
+        const uint32_t bits = id == p ? patch_bits(r & 7, (r >> 3) & 7, (r >> 6) & 7, r >> 9) : 0u;
+        if (!list_entries<WRITE, 8>(bits, e, 0, n, pcap, out)) return;
+      }
+      k = kn;
+      e = en;
+    }
+    if (!WRITE) {
+      table[(uint64_t)(c + patch) * 64 + lane] = n;
+      if (i1 == S && lane == 0) ranges[patch].y = S;
+    }
+  }
+}
+
+// Lists straight from the depth-sorted entries: a workgroup tests a chunk of
+// them (STEPS x 64 per wavefront) against one patch and collects those that
+// touch it in LDS.  To count, each wavefront takes every fourth 64 of them; to
+// write, each takes all of them for two of the patch's rows of tiles (the
+// writes of one tile follow each other, and a wavefront's walk over a full
+// chunk is a quarter as long).  Row patch * chunks + chunk of the table.
+template <bool WRITE, int STEPS>
+__global__ void __launch_bounds__(kBlock) k_entry_lists(ViewTable vt, const uint32_t* __restrict__ rect0,
+                                                        const uint32_t* __restrict__ rect1,
+                                                        const uint32_t* __restrict__ dval,
+                                                        uint32_t* __restrict__ counters, uint32_t pcap,
+                                                        uint32_t* __restrict__ table,
+                                                        const uint2* __restrict__ ranges, uint32_t* __restrict__ out,
+                                                        uint32_t* __restrict__ order_state,
+                                                        uint32_t* __restrict__ order) {
+  constexpr uint32_t kEntries = kBlock * STEPS;
+  __shared__ uint32_t s_bits[kEntries], s_e[WRITE ? kEntries : 1], s_n[kWaves][64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t u = blockIdx.x;
+  if (WRITE) {  // the first workgroups order the tiles
+    const uint32_t wgs = order_wgs((uint32_t)vt.total_tiles);
+    if (u < wgs) {
+      order_tiles(ranges, (uint32_t)vt.total_tiles, u, order_state, order);
+      return;
+    }
+    u -= wgs;
+  }
+  if (overflowed(counters, pcap)) {
+    if (!WRITE && blockIdx.x == 0 && threadIdx.x == 0) counters[2] = 1u;
+    return;
+  }
+  const uint32_t nb = counters[0];
+  const uint32_t nchunk = (nb + kEntries - 1) / kEntries;
+  const uint32_t units = nchunk * (uint32_t)vt.total_patches;
+  if (u >= units) return;
+  const uint32_t patch = u / nchunk, c = u - patch * nchunk;
+  const uint32_t view = (uint32_t)patch_view(vt, patch);
+  const ViewDesc& vd = vt.v[view];
+  const int npx = (vd.ntx + 7) >> 3, local = (int)patch - vd.patch_base, py = local / npx, px = local - py * npx;
+  uint32_t* row = table + ((uint64_t)patch * nchunk + c) * 64;
+  // the rectangles, in tiles from the patch's first, and which of them touch it
+  const uint32_t i0 = c * kEntries + wv * (64 * STEPS) + lane;
+  uint32_t a[STEPS], b[STEPS], e[STEPS];
+#pragma unroll
+  for (int s = 0; s < STEPS; s++) {
+    const uint32_t i = i0 + 64 * s;
+    a[s] = i < nb ? rect0[i] : ~0u;  // (no such view)
+    b[s] = i < nb ? rect1[i] : 0u;
+    e[s] = WRITE && i < nb ? dval[i] : 0u;
+  }
+  uint32_t n = 0;
+  if (WRITE) {
+    const int t = 16 * wv + (lane & 15);  // lanes 0 .. 15: the wavefront's two rows of tiles
+    const int tile = patch_tile(vd, px, py, t);
+    n = row[t] + (tile >= 0 ? ranges[tile].x : 0u);
+  }
+  uint64_t m[STEPS];
+  uint32_t mine = 0;
+#pragma unroll
+  for (int s = 0; s < STEPS; s++) {
+    const int x0 = (int)(a[s] & 2047u) - 8 * px, x1 = (int)((a[s] >> 11) & 2047u) - 8 * px;
+    const int y0 = (int)(b[s] & 2047u) - 8 * py, y1 = (int)((b[s] >> 11) & 2047u) - 8 * py;
+    const bool hit = a[s] >> 22 == view && x0 < 8 && x1 >= 0 && y0 < 8 && y1 >= 0;
+    a[s] = hit ? patch_bits(max(x0, 0), min(x1, 7), max(y0, 0), min(y1, 7)) : 0u;
+    m[s] = __ballot(hit);
+    mine += (uint32_t)__popcll(m[s]);
+  }
+  if (lane == 0) s_n[wv][0] = mine;
+  __syncthreads();
+  uint32_t nh = 0, at = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; w++) {
+    at += w < wv ? s_n[w][0] : 0u;
+    nh += s_n[w][0];
+  }
+#pragma unroll
+  for (int s = 0; s < STEPS; s++) {
+    if (a[s]) {
+      const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[s] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[s], at));
+      s_bits[k] = a[s];
+      if (WRITE) s_e[k] = e[s];
+    }
+    at += (uint32_t)__popcll(m[s]);
+  }
+  __syncthreads();
+  if constexpr (WRITE) {
+    arrived(n);
+    for (uint32_t k = 0; k < nh; k += 64) {
+      const bool in = k + lane < nh;
+      if (!list_entries<true, 2>(in ? s_bits[k + lane] : 0u, in ? s_e[k + lane] : 0u, 2 * wv, n, pcap, out)) return;
+    }
+  } else {
+    for (uint32_t k = 64 * wv; k < nh; k += kBlock)
+      list_entries<false, 8>(k + lane < nh ? s_bits[k + lane] : 0u, 0u, 0, n, pcap, out);
+    s_n[wv][lane] = n;
+    __syncthreads();
+    if (wv == 0) row[lane] = s_n[0][lane] + s_n[1][lane] + s_n[2][lane] + s_n[3][lane];
+  }
+}
+
+// One workgroup per patch: the rows of its chunks become exclusive prefixes,
+// and their sums the tiles' pair counts.  chunk: that of k_entry_lists, or 0
+// for k_item_lists.  Also counts the tiles' buckets of the order.  Workgroups past the patches zero the screen-space gradient
+// accumulators of the binned entries (when g2d is given) for the backward that
+// may follow.
+constexpr int kScanThreads = 1024;
+__global__ void __launch_bounds__(kScanThreads) k_list_scan(ViewTable vt, const uint2* __restrict__ ranges,
+                                                            const uint32_t* __restrict__ counters, uint32_t pcap,
+                                                            uint32_t chunk, uint32_t* __restrict__ table,
+                                                            uint32_t* __restrict__ tile_count,
+                                                            uint32_t* __restrict__ order_state,
+                                                            const uint32_t* __restrict__ tiles, int64_t E,
+                                                            float* __restrict__ g2d) {
+  constexpr int kW = kScanThreads / 64;
+  __shared__ uint32_t s_n[kW][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const uint32_t patch = blockIdx.x;
+  if (patch >= (uint32_t)vt.total_patches) {
+    zero_g2d_entry((int64_t)(patch - vt.total_patches) * kScanThreads + threadIdx.x, tiles, E, g2d);
+    return;
+  }
+  uint32_t c0 = 0, c1 = 0;  // the patch's rows
+  uint64_t row0 = patch;    // of chunk 0
+  if (!overflowed(counters, pcap)) {
+    if (chunk) {
+      c1 = (counters[0] + chunk - 1) / chunk;
+      row0 = (uint64_t)patch * c1;
+    } else {
+      const uint2 r = ranges[patch];  // (UINT_MAX, 0) for a patch without items
+      if (r.x < r.y) {
+        c0 = r.x / kListItems;
+        c1 = (r.y - 1) / kListItems + 1;
+      }
+    }
+  }
+  const uint32_t per = (c1 - c0 + kW - 1) / kW;
+  const uint32_t b = min(c0 + wv * per, c1), e = min(b + per, c1);
+  uint32_t* row = table + row0 * 64 + lane;
+  uint32_t sum = 0;
+#pragma unroll 8
+  for (uint32_t c = b; c < e; c++) sum += row[(uint64_t)c * 64];
+  s_n[wv][lane] = sum;
+  __syncthreads();
+  uint32_t pre = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kW; w++) {
+    const uint32_t v = s_n[w][lane];
+    pre += w < wv ? v : 0u;
+    total += v;
+  }
+#pragma unroll 8
+  for (uint32_t c = b; c < e; c++) {
+    const uint32_t v = row[(uint64_t)c * 64];
+    row[(uint64_t)c * 64] = pre;
+    pre += v;
+  }
+  if (wv == 0) {
+    const int tile = patch_tile(vt, patch, lane);
+    if (tile >= 0) tile_count[tile] = total;
+    uint32_t n = 0;
+    bucket_add(n, tile >= 0 ? order_bucket(total) : -1);
+    if (n) atomicAdd(&order_state[patch % kOrderCopies * 64 + lane], n);
   }
 }
 
@@ -956,13 +1291,36 @@ RadixState depth_state(const SortBuffers& b) {
 }
 }  // namespace
 
+// Whether a workgroup per patch and chunk tests every sorted entry
+// (k_entry_lists) or the entries are sorted by patch first (k_item_lists), which
+// takes five launches more, but no time per patch.  The stage's time: 300k
+// Gaussians in one 800x800 view, 14M tests, 130 us testing and 159 sorting; 500k
+// in one 1600x900 view, 50M tests, 220 and 196.
+namespace {
+inline bool test_entries(int64_t E, int64_t patches) { return E * patches <= (1ll << 25); }
+// Entries per workgroup of the tests: 1,024 collect more of a patch's entries
+// at once, 256 make enough workgroups of a small call (1.5M tests: the same;
+// 4M: 82 us with 1,024 and 91 with 256).
+inline uint32_t entry_chunk(int64_t E, int64_t patches) { return kBlock * (E * patches <= (1ll << 20) ? 1u : 4u); }
+
+// the tile scan's look-back words stand between the tickets and the tables
+inline int64_t tile_scan_words(int64_t total_tiles) { return 2 * ((total_tiles + kChunk - 1) / kChunk + 1); }
+inline int64_t pair_zero_words(int64_t total_tiles) {
+  return ((kGhCopies + 1) * kGhStride + tile_scan_words(total_tiles) + 3) / 4 * 4;
+}
+RadixState pair_state(const SortBuffers& b, int64_t bound, int items) {
+  return radix_state(b.rstate_pairs, bound, items, false,
+                     pair_zero_words(b.total_tiles) - (kGhCopies + 1) * kGhStride);
+}
+}  // namespace
+
 // One preparation for the whole stage: the depth sort's state, the pair
 // sort's histograms, the tile ranges, the tile order's counts and the
 // backward work-item count.
 BinPrep bin_prep(const SortBuffers& b) {
   const RadixState rs = depth_state(b);
   BinPrep bp{{b.rstate_depth, b.order_state, b.n_items, b.rstate_pairs},
-             {rs.words(), (int64_t)kOrderStateWords, 1, (kGhCopies + 1) * kGhStride},
+             {rs.words(), (int64_t)kOrderStateWords, 1, pair_zero_words(b.total_tiles)},
              b.ranges,
              b.total_tiles,
              0};
@@ -971,105 +1329,129 @@ BinPrep bin_prep(const SortBuffers& b) {
   return bp;
 }
 
-void launch_bin_count(SortBuffers& b, bool prepped, hipStream_t st) {
+void launch_bin_count(SortBuffers& b, const ViewTable& vt, bool prepped, hipStream_t st) {
   const uint32_t E = (uint32_t)b.E;
   const RadixState rs = depth_state(b);
   const RadixPlan plan{4, 8};
   if (!prepped) {
     const ZeroList z{{b.order_state, b.n_items, b.rstate_pairs, nullptr},
-                     {(int64_t)kOrderStateWords, 1, (kGhCopies + 1) * kGhStride, 0}};
+                     {(int64_t)kOrderStateWords, 1, pair_zero_words(b.total_tiles), 0}};
     int64_t prep = rs.words() / 4;
     for (int k = 0; k < 3; k++) prep = std::max(prep, z.n[k]);
     prep = std::max(prep, b.total_tiles);
     hipLaunchKernelGGL(k_stage_prep, dim3((unsigned)((prep + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, rs,
                        rs.words(), z, b.ranges, b.total_tiles, (const uint32_t*)b.counters,
-                       (const uint32_t*)nullptr, (const uint32_t*)nullptr, (const uint32_t*)nullptr, 0u,
-                       (uint32_t*)nullptr, (int64_t)0, 0u);
+                       (const uint32_t*)nullptr, (const uint32_t*)nullptr, 0u, (uint32_t*)nullptr, (int64_t)0, 0u);
   }
   // compaction of the binned entries with their depth keys, and the depth keys' digit histograms
-  scan1<true>(BinnedFlag{b.tiles}, CompactDepth{b.depth, b.dkey[0], b.dval[0]}, nullptr, E, E, b.E,
-              rs.tickets + kMaxPasses, rs.scan_status, &b.counters[0], rs.ghist, &b.counters[3], st);
+  uint32_t* psum = rs.tickets + 256;
+  scan1<true>(TileCount{b.tiles}, CompactDepth{b.depth, b.dkey[0], b.dval[0]}, nullptr, E, E, b.E,
+              rs.tickets + kMaxPasses, rs.scan_status, &b.counters[0], rs.ghist, psum, &b.counters[3], st);
   // depth order (stable: equal depths keep entry order)
   b.dsorted = radix_sort(b.dkey, b.dval, &b.counters[0], b.E, plan, rs, &b.counters[3], st);
-  // pair offsets in depth order
-  scan1<false>(SortedTiles{b.tiles, b.dval[b.dsorted]},
-               StoreOffset{b.poff, b.blk_start, b.nblk_start, (int64_t)kBlock * pair_items(b.pcap)},
-               &b.counters[0], 0u, E, b.E,
-               rs.tickets + kMaxPasses + 1, rs.scan_status + rs.nscan, &b.counters[1], (uint32_t*)nullptr,
-               &b.counters[3], st);
+  hipLaunchKernelGGL(k_rects, dim3(std::max(1u, (E + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, vt, b.rec,
+                     (const uint32_t*)b.dval[b.dsorted], (const uint32_t*)psum, b.counters, b.dkey[0], b.dkey[1]);
+  // item offsets in depth order
+  if (!test_entries(b.E, b.total_patches))
+    scan1<false>(PatchCount{b.dkey[0], b.dkey[1]},
+                 StoreOffset{b.poff, b.blk_start, b.nblk_start, (int64_t)kBlock * sort_items(b.pcap)},
+                 &b.counters[0], 0u, E, b.E, rs.tickets + kMaxPasses + 1, rs.scan_status + rs.nscan, &b.counters[7],
+                 (uint32_t*)nullptr, (uint32_t*)nullptr, &b.counters[3], st);
 }
 
-void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t pairs_hint, bool regrown, hipStream_t st) {
-  int bits = 1;
-  while ((1ll << bits) < (int64_t)vt.total_tiles) bits++;
-  const RadixPlan plan = radix_plan(bits);
-  const int64_t bound = pairs_hint < b.pcap ? pairs_hint : b.pcap;
-  const int items = pair_items(b.pcap);
-  const uint32_t chunk = (uint32_t)(kBlock * items);
-  const RadixState rs = radix_state(b.rstate_pairs, bound, items, false);
+void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t items_hint, bool regrown, hipStream_t st) {
+  const bool direct = test_entries(b.E, b.total_patches);
+  const int64_t bound = direct ? 0 : items_hint < b.pcap ? items_hint : b.pcap;
+  const int items = sort_items(b.pcap);
+  const uint32_t chunk = (uint32_t)(kBlock * items), cap = (uint32_t)b.pcap;
+  const RadixState rs = pair_state(b, bound, items);
+  uint32_t* count = &b.counters[7];
   if (regrown) {
-    // the passes write every table entry they read: only the histograms (and
-    // the unused tickets) start from zero
-    const int64_t zero_words = (kGhCopies + 1) * kGhStride;
+    // the passes write every table entry they read: only the histograms, the
+    // tickets and the tile scan's state start from zero
+    const int64_t zero_words = pair_zero_words(b.total_tiles);
     const ZeroList z{{nullptr, nullptr, nullptr, nullptr}, {0, 0, 0, 0}};
-    const int64_t prep = std::max<int64_t>(zero_words / 4, b.E);
+    const int64_t prep = std::max<int64_t>(zero_words / 4, direct ? 0 : b.E);
     hipLaunchKernelGGL(k_stage_prep, dim3((unsigned)((prep + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, rs,
-                       zero_words, z, (uint2*)nullptr, (int64_t)0, (const uint32_t*)b.counters,
-                       (const uint32_t*)b.tiles, (const uint32_t*)b.dval[b.dsorted], (const uint32_t*)b.poff,
-                       (uint32_t)b.pcap, b.blk_start, rs.nblk, chunk);
+                       zero_words, z, (uint2*)nullptr, (int64_t)0, (const uint32_t*)b.counters, (const uint32_t*)count,
+                       (const uint32_t*)b.poff, cap, direct ? nullptr : b.blk_start, rs.nblk, chunk);
   }
-  // the pairs, with every pass's digit histogram and the first pass's per-chunk
-  // counts; then the passes, each a scan of the chunk counts and a scatter
-  // (the chunk counts of later passes taken from their input)
+  const uint32_t* const rect0 = b.dkey[0];
+  const uint32_t* const rect1 = b.dkey[1];
+  const uint32_t* const dval = b.dval[b.dsorted];
+  uint32_t* const table = rs.status;
+  const uint32_t T = (uint32_t)b.total_tiles;
+  // the scan of the tiles' counts, which stand in the tile order's place
+  auto ranges_of = [&](uint32_t list_chunk) {
+    const unsigned gz = b.g2d ? (unsigned)((b.E + kScanThreads - 1) / kScanThreads) : 0u;
+    hipLaunchKernelGGL(k_list_scan, dim3((unsigned)b.total_patches + gz), dim3(kScanThreads), 0, st, vt,
+                       (const uint2*)b.ranges, (const uint32_t*)b.counters, cap, list_chunk, table, b.tile_order,
+                       b.order_state, (const uint32_t*)b.tiles, b.E, b.g2d);
+    scan1<false>(CountVal{b.tile_order}, StoreRange{b.ranges}, nullptr, T, T, T, rs.tickets,
+                 reinterpret_cast<uint64_t*>(rs.tickets + kGhStride), (uint32_t*)nullptr, (uint32_t*)nullptr,
+                 (uint32_t*)nullptr, &b.counters[3], st);
+  };
+  const unsigned ow = order_wgs(T);
   int cur = 0;
-  if (rs.nblk) {
+  if (direct) {
+    const uint32_t lc = entry_chunk(b.E, b.total_patches);
+    const int64_t units = (b.E + lc - 1) / lc * b.total_patches;
+    if (units)
+      hipLaunchKernelGGL((lc == kBlock ? k_entry_lists<false, 1> : k_entry_lists<false, 4>), dim3((unsigned)units),
+                         dim3(kBlock), 0, st, vt, rect0, rect1, dval, b.counters, cap, table, (const uint2*)b.ranges,
+                         b.pval[0], b.order_state, b.tile_order);
+    ranges_of(lc);
+    if (units + ow)
+      hipLaunchKernelGGL((lc == kBlock ? k_entry_lists<true, 1> : k_entry_lists<true, 4>), dim3((unsigned)units + ow),
+                         dim3(kBlock), 0, st, vt, rect0, rect1, dval, b.counters, cap, table, (const uint2*)b.ranges,
+                         b.pval[0], b.order_state, b.tile_order);
+  } else {
+    // the items, with every pass's digit histogram and the first pass's per-chunk
+    // counts; then the passes, each a scan of the chunk counts and a scatter
+    // (the chunk counts of later passes taken from their input)
+    int bits = 1;
+    while ((1ll << bits) < b.total_patches) bits++;
+    const RadixPlan plan = radix_plan(bits);
+    const uint32_t bound32 = (uint32_t)bound;
     const int64_t nb = rs.nblk;
-    const uint32_t cap = (uint32_t)bound;
-    hipLaunchKernelGGL(k_emit, dim3((unsigned)nb), dim3(kBlock), 0, st, vt, b.rec, b.dval[b.dsorted], b.poff,
-                       b.blk_start, b.counters, (uint32_t)b.pcap, plan.npass, plan.dbits, rs.ghist, b.pkey[0],
-                       b.pval[0], rs.status, chunk);
-    for (int p = 0; p < plan.npass; p++) {
-      uint32_t* table = rs.status + (int64_t)p * nb * 256;
-      const int shift = p * plan.dbits;
-      if (p > 0)
-        hipLaunchKernelGGL(items == kRItems ? k_digit_count<kRItems> : k_digit_count<kRItemsSmall>, dim3((unsigned)nb),
-                           dim3(kBlock), 0, st, b.pkey[cur],
-                           (const uint32_t*)&b.counters[1], cap, shift, plan.dbits, table, nb);
-      hipLaunchKernelGGL(k_digit_scan, dim3(1u << plan.dbits), dim3(kBlock), 0, st, table, nb,
-                         (const uint32_t*)&b.counters[1], cap, (int)chunk, (const uint32_t*)(rs.ghist + p * 256));
-      const bool last = p == plan.npass - 1;
-      hipLaunchKernelGGL(items == kRItems ? k_digit_scatter<kRItems> : k_digit_scatter<kRItemsSmall>,
-                         dim3((unsigned)nb), dim3(kBlock), 0, st, b.pkey[cur],
-                         b.pval[cur], b.pkey[cur ^ 1], b.pval[cur ^ 1], (const uint32_t*)&b.counters[1], cap, shift,
-                         plan.dbits, (const uint32_t*)table, nb, last ? b.ranges : nullptr,
-                         (uint32_t)vt.total_tiles, (const uint32_t*)b.counters, (uint32_t)b.pcap);
-      cur ^= 1;
+    if (nb) {
+      hipLaunchKernelGGL(k_emit, dim3((unsigned)nb), dim3(kBlock), 0, st, vt, rect0, rect1, dval, b.poff, b.blk_start,
+                         b.counters, cap, plan.npass, plan.dbits, rs.ghist, b.pkey[0], b.pval[0], rs.status, chunk);
+      for (int p = 0; p < plan.npass; p++) {
+        uint32_t* tp = rs.status + (int64_t)p * nb * 256;
+        const int shift = p * plan.dbits;
+        if (p > 0)
+          hipLaunchKernelGGL(items == kRItems ? k_digit_count<kRItems> : k_digit_count<kRItemsSmall>,
+                             dim3((unsigned)nb), dim3(kBlock), 0, st, b.pkey[cur], count, bound32, shift, plan.dbits,
+                             tp, nb);
+        hipLaunchKernelGGL(k_digit_scan, dim3(1u << plan.dbits), dim3(kBlock), 0, st, tp, nb, count, bound32,
+                           (int)chunk, (const uint32_t*)(rs.ghist + p * 256));
+        hipLaunchKernelGGL(items == kRItems ? k_digit_scatter<kRItems> : k_digit_scatter<kRItemsSmall>,
+                           dim3((unsigned)nb), dim3(kBlock), 0, st, b.pkey[cur], b.pval[cur], b.pkey[cur ^ 1],
+                           b.pval[cur ^ 1], count, bound32, shift, plan.dbits, (const uint32_t*)tp, nb);
+        cur ^= 1;
+      }
     }
+    const int64_t units = (bound + kListItems * kWaves - 1) / (kListItems * kWaves);
+    const unsigned grid = (unsigned)std::min<int64_t>((units + 7) / 8 * 8, kListWG);
+    const uint32_t* const k = b.pkey[cur];
+    const uint32_t* const v = b.pval[cur];
+    if (units)
+      hipLaunchKernelGGL(k_item_lists<false>, dim3(grid), dim3(kBlock), 0, st, vt, k, v, (const uint32_t*)b.counters,
+                         cap, table, b.ranges, b.pval[cur ^ 1], b.order_state, b.tile_order);
+    ranges_of(0);
+    if (grid + ow)
+      hipLaunchKernelGGL(k_item_lists<true>, dim3(grid + ow), dim3(kBlock), 0, st, vt, k, v,
+                         (const uint32_t*)b.counters, cap, table, b.ranges, b.pval[cur ^ 1], b.order_state,
+                         b.tile_order);
+    cur ^= 1;
   }
   b.psorted = cur;
-  // the tile order, and the gradient accumulators cleared for a backward
-  const unsigned gz = b.g2d ? (unsigned)((b.E + kOrderThreads - 1) / kOrderThreads) : 0u;
-  const uint32_t T = (uint32_t)vt.total_tiles;
-  if (T <= kOrderOneGroup) {
-    if (T > 0 || gz)
-      hipLaunchKernelGGL(k_tile_order, dim3(1 + gz), dim3(kOrderThreads), 0, st, b.ranges, T,
-                         b.tile_order, (const uint32_t*)b.tiles, b.E, b.g2d);
-  } else {
-    const uint32_t ng = (T + kOrderGroupTiles - 1) / kOrderGroupTiles;
-    hipLaunchKernelGGL(k_order_count, dim3(ng + gz), dim3(kOrderThreads), 0, st, b.ranges, T, ng,
-                       b.order_state, (const uint32_t*)b.tiles, b.E, b.g2d);
-    hipLaunchKernelGGL(k_order_place, dim3(ng), dim3(kOrderThreads), 0, st, b.ranges, T,
-                       b.order_state, b.tile_order);
-  }
 }
 
 int64_t chunk_scan_words(int64_t n) { return 2 + 2 * ((n + kChunk - 1) / kChunk + 1); }
 
 namespace {
-struct CountVal {
-  const uint32_t* c;
-  __device__ uint32_t operator()(int64_t i) const { return c[i]; }
-};
 struct CountOffset {
   uint32_t* off;
   __device__ void operator()(int64_t i, uint32_t pre, uint32_t) const { off[i] = pre; }
@@ -1086,12 +1468,20 @@ void launch_count_scan(const uint32_t* cnt, int64_t n, uint32_t* off, uint32_t* 
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, state, words);
   const uint32_t N = (uint32_t)n;
   scan1<false>(CountVal{cnt}, CountOffset{off}, nullptr, N, N, n, state, reinterpret_cast<uint64_t*>(state + 2), total,
-               (uint32_t*)nullptr, err, st);
+               (uint32_t*)nullptr, (uint32_t*)nullptr, err, st);
 }
 
 int64_t sort_state_words(int64_t bound, bool pairs) {
   // the pair state sized for the smaller blocks, whichever pair_items picks
   return radix_state(nullptr, bound, kRItemsSmall, !pairs).words();
+}
+// (the rows of sorted items take the place of the passes' tables, which have
+// twice as many words)
+int64_t list_state_words(int64_t E, int64_t total_tiles, int64_t total_patches) {
+  const int64_t rows = test_entries(E, total_patches)
+                           ? total_patches * ((E + entry_chunk(E, total_patches) - 1) / entry_chunk(E, total_patches))
+                           : 0;
+  return tile_scan_words(total_tiles) + 4 + 64 * (rows + total_patches + 2);
 }
 int64_t sort_block_starts(int64_t pcap) { return radix_blocks(pcap, kRItemsSmall) + 1; }
 int64_t order_state_words() { return kOrderStateWords; }
