@@ -1,7 +1,7 @@
 // Integer stage of the rasteriser on gfx950: compaction of the binned entries,
-// an LSD radix sort of their float32 depths, and the tiles' lists -- for every
-// tile the entries that touch it, in depth order -- with their [start, end)
-// ranges.  The (tile, entry) pairs are never sorted: a wavefront takes 64
+// the sort of their float32 depths (LSD radix, or by counting where they are
+// few), and the tiles' lists -- for every tile the entries that touch it, in
+// depth order -- with their [start, end) ranges.  The (tile, entry) pairs are never sorted: a wavefront takes 64
 // depth-ordered entries and a patch of 8 x 8 tiles, and ballots of the columns
 // and rows that the entries cover give each tile its entries, so a pair costs
 // one write.  Which entries touch a patch is found by testing them all where
@@ -57,7 +57,7 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t& total)
 }
 
 // ------------------------------------------------------------ radix sort
-// The depth order's passes (the pair sort's are further below): one kernel
+// The depth order's passes (the item sort's are further below): one kernel
 // per pass, where each workgroup takes the next 4096 items in ticket
 // order, ranks them stably by digit in LDS, and finds where its items of each
 // digit go by looking back over the per-digit counts that earlier workgroups
@@ -98,6 +98,19 @@ __device__ __forceinline__ uint32_t ghist_total(const uint32_t* g, int d) {
   return s;
 }
 
+// Up to this many entries the depth sort counts, for each, the entries before
+// it (k_rank).  The four radix passes take 26 us of 476 entries and 31 of 9,300:
+// each waits for the one before and for earlier workgroups' counts.  Counting
+// takes 5 and 15, but n^2 / 64 comparisons: all of 15,000 entries binned, the
+// stage takes 73 us with it and 84 with the passes, all of 20,000, 85 and 85
+// (half of 30,000, 72 and 83, but half is not promised).
+constexpr int64_t kRankEntries = 20480;
+// Entries that a wavefront of it compares 256 with: more wavefronts for the
+// fewest, fewer atomic adds to each place for more (9,300 entries: 34 us with
+// segments of 16, 20 of 32, 15 of 64).
+inline uint32_t rank_segment(int64_t E) { return E <= 2048 ? 16u : 64u; }
+inline bool rank_entries(int64_t E) { return E <= kRankEntries; }
+
 // Radix state of one sort: global digit histograms, tickets and look-back
 // status words, laid out in one buffer.
 struct RadixState {
@@ -106,9 +119,10 @@ struct RadixState {
   uint32_t* status;       // [kMaxPasses][nblk][256]: look-back words (depth sort), chunk tables (pair sort)
   uint64_t* scan_status;  // [2][nscan] look-back words of the two scans over entries
   int64_t nblk, nscan;
+  int64_t nplace;         // words after the scans' for the places of a short depth sort
   int items;              // items per thread of the passes
   __host__ __device__ int64_t words() const {
-    return (int64_t)kMaxPasses * 256 * (nblk + 1 + kGhCopies) + 4 * nscan;
+    return (int64_t)kMaxPasses * 256 * (nblk + 1 + kGhCopies) + 4 * nscan + nplace;
   }
 };
 
@@ -123,6 +137,7 @@ RadixState radix_state(uint32_t* base, int64_t bound, int items, bool with_scans
   r.items = items;
   r.nblk = radix_blocks(bound, items);
   r.nscan = with_scans ? (bound + kChunk - 1) / kChunk : 0;
+  r.nplace = with_scans && rank_entries(bound) ? (bound + 3) / 4 * 4 : 0;
   r.ghist = base;
   r.tickets = base + kGhCopies * kGhStride;
   r.status = base + (kGhCopies + 1) * kGhStride + extra;
@@ -210,7 +225,7 @@ constexpr int kPsum = 16, kPsumStride = 32;  // words of one sum, a cache line a
 // their prefixes through look-back words; the workgroup holding the last item
 // writes the total.  With HIST, g.key(i) of every item with a non-zero value
 // also enters the digit histograms of a 4-pass, 8-bit radix sort.
-template <class F, class G, bool HIST>
+template <class F, class G, bool FLAGS, bool HIST>
 __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap,
                                                   uint32_t* ticket, uint64_t* status, uint32_t* total_out,
                                                   uint32_t* ghist, uint32_t* psum, uint32_t* err) {
@@ -238,7 +253,7 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
     v[k] = (base + k < count) ? f(base + k) : 0u;
     sum += v[k];
   }
-  if constexpr (HIST) {
+  if constexpr (FLAGS) {
     uint32_t all;
     block_scan_excl(sum, all);
     if (t == 0 && all) atomicAdd(&psum[blk % kPsum * kPsumStride], all);
@@ -289,12 +304,12 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
   }
 }
 
-template <bool HIST, class F, class G>
+template <bool FLAGS, bool HIST, class F, class G>
 void scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap, int64_t bound, uint32_t* ticket,
            uint64_t* status, uint32_t* total_out, uint32_t* ghist, uint32_t* psum, uint32_t* err, hipStream_t st) {
   int64_t nb = (bound + kChunk - 1) / kChunk;
   if (nb < 1) nb = 1;  // one workgroup writes a zero total
-  hipLaunchKernelGGL((k_scan1<F, G, HIST>), dim3((unsigned)nb), dim3(kBlock), 0, st, f, g, count_ptr, fixed, cap,
+  hipLaunchKernelGGL((k_scan1<F, G, FLAGS, HIST>), dim3((unsigned)nb), dim3(kBlock), 0, st, f, g, count_ptr, fixed, cap,
                      ticket, status, total_out, ghist, psum, err);
 }
 
@@ -448,7 +463,7 @@ __global__ void __launch_bounds__(kBlock) k_onesweep(const uint32_t* __restrict_
 }
 
 // ---------------------------------------------------- reduce-then-scan passes
-// The pair sort's passes in three launches with no chain between workgroups
+// The item sort's passes in three launches with no chain between workgroups
 // (the wait on earlier workgroups' counts dominated the one-kernel passes at
 // a few thousand workgroups, and the emission counts the first pass's chunks
 // for free):
@@ -661,11 +676,52 @@ __device__ __forceinline__ uint2 entry_rect(const ViewTable& vt, const Rec* rec,
   return make_uint2((uint32_t)(x0 | (x1 - 1) << 11) | view << 22, (uint32_t)(y0 | (y1 - 1) << 11));
 }
 
+// A short depth sort by counting: entry i's place is the number of entries j
+// before it in (key, j) order.  A wavefront compares 256 entries with a segment
+// of them and adds its counts to the entries' places (zero before).
+__global__ void __launch_bounds__(kBlock) k_rank(const uint32_t* __restrict__ key,
+                                                 const uint32_t* __restrict__ counters, uint32_t segment,
+                                                 uint32_t* __restrict__ place) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t n = counters[0];
+  const uint32_t i0 = (blockIdx.x * kWaves + wv) * 256, j0 = blockIdx.y * segment;
+  if (i0 >= n || j0 >= n) return;
+  const uint32_t kj = j0 + lane < n ? key[j0 + lane] : ~0u;  // (nothing is after these)
+  uint32_t k[4], c[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const uint32_t i = i0 + 64 * r + lane;
+    k[r] = i < n ? key[i] : 0u;
+  }
+  if (j0 >= i0 && j0 < i0 + 256) {  // the segment is in the wavefront's own 256: equal keys before i count
+    const int own = (int)(j0 - i0) >> 6, off = (int)(j0 - i0) & 63;
+    uint32_t ties = 0;
+    for (int j = 0; j < (int)segment; j++)
+      ties += (uint32_t)__builtin_amdgcn_readlane(kj, j) == (own == 0 ? k[0] : own == 1 ? k[1] : own == 2 ? k[2] : k[3]) && off + j < lane ? 1u : 0u;
+#pragma unroll
+    for (int r = 0; r < 4; r++) c[r] = r == own ? ties : 0u;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; r++) k[r] += j0 < i0 + 64 * r ? 1u : 0u;  // all before i: equal ones count (keys are below 2^31)
+#pragma unroll 8
+  for (int j = 0; j < (int)segment; j++) {
+    const uint32_t q = (uint32_t)__builtin_amdgcn_readlane(kj, j);
+#pragma unroll
+    for (int r = 0; r < 4; r++) c[r] += q < k[r] ? 1u : 0u;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; r++)
+    if (i0 + 64 * r + lane < n && c[r]) atomicAdd(&place[i0 + 64 * r + lane], c[r]);
+}
+
 // All sorted entries' rectangles, and the pair count from its partial sums.
+// place: nullptr, or where each entry of the compacted list goes (then dsorted
+// is written as well).
 __global__ void __launch_bounds__(kBlock) k_rects(ViewTable vt, const Rec* __restrict__ rec,
-                                                  const uint32_t* __restrict__ dval, const uint32_t* __restrict__ psum,
-                                                  uint32_t* __restrict__ counters, uint32_t* __restrict__ rect0,
-                                                  uint32_t* __restrict__ rect1) {
+                                                  const uint32_t* __restrict__ dval,
+                                                  const uint32_t* __restrict__ place, uint32_t* __restrict__ dsorted,
+                                                  const uint32_t* __restrict__ psum, uint32_t* __restrict__ counters,
+                                                  uint32_t* __restrict__ rect0, uint32_t* __restrict__ rect1) {
   const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
   if (blockIdx.x == 0 && threadIdx.x < 64) {
     const uint32_t s = wave_scan_incl(threadIdx.x < kPsum ? psum[threadIdx.x * kPsumStride] : 0u);
@@ -675,9 +731,16 @@ __global__ void __launch_bounds__(kBlock) k_rects(ViewTable vt, const Rec* __res
     }
   }
   if (i >= counters[0]) return;
-  const uint2 r = entry_rect(vt, rec, dval[i]);
-  rect0[i] = r.x;
-  rect1[i] = r.y;
+  const uint32_t e = dval[i];
+  const uint2 r = entry_rect(vt, rec, e);
+  uint32_t at = i;
+  if (place) {
+    at = place[i];
+    if (at >= counters[0]) return;  // never; guards the buffers
+    dsorted[at] = e;
+  }
+  rect0[at] = r.x;
+  rect1[at] = r.y;
 }
 
 // The patches that a sorted entry's rectangle touches.
@@ -1343,17 +1406,33 @@ void launch_bin_count(SortBuffers& b, const ViewTable& vt, bool prepped, hipStre
                        rs.words(), z, b.ranges, b.total_tiles, (const uint32_t*)b.counters,
                        (const uint32_t*)nullptr, (const uint32_t*)nullptr, 0u, (uint32_t*)nullptr, (int64_t)0, 0u);
   }
-  // compaction of the binned entries with their depth keys, and the depth keys' digit histograms
+  // compaction of the binned entries with their depth keys, and for the passes the keys' digit histograms
   uint32_t* psum = rs.tickets + 256;
-  scan1<true>(TileCount{b.tiles}, CompactDepth{b.depth, b.dkey[0], b.dval[0]}, nullptr, E, E, b.E,
-              rs.tickets + kMaxPasses, rs.scan_status, &b.counters[0], rs.ghist, psum, &b.counters[3], st);
+  const TileCount tc{b.tiles};
+  const CompactDepth cd{b.depth, b.dkey[0], b.dval[0]};
+  uint32_t* ticket = rs.tickets + kMaxPasses;
+  uint32_t* place = nullptr;
   // depth order (stable: equal depths keep entry order)
-  b.dsorted = radix_sort(b.dkey, b.dval, &b.counters[0], b.E, plan, rs, &b.counters[3], st);
+  if (rank_entries(b.E)) {
+    place = reinterpret_cast<uint32_t*>(rs.scan_status + 2 * rs.nscan);
+    scan1<true, false>(tc, cd, nullptr, E, E, b.E, ticket, rs.scan_status, &b.counters[0], (uint32_t*)nullptr, psum,
+                       &b.counters[3], st);
+    const uint32_t segment = rank_segment(b.E);
+    if (E)
+      hipLaunchKernelGGL(k_rank, dim3((E + kBlock * 4 - 1) / (kBlock * 4), (E + segment - 1) / segment), dim3(kBlock),
+                         0, st, (const uint32_t*)b.dkey[0], (const uint32_t*)b.counters, segment, place);
+    b.dsorted = 1;
+  } else {
+    scan1<true, true>(tc, cd, nullptr, E, E, b.E, ticket, rs.scan_status, &b.counters[0], rs.ghist, psum,
+                      &b.counters[3], st);
+    b.dsorted = radix_sort(b.dkey, b.dval, &b.counters[0], b.E, plan, rs, &b.counters[3], st);
+  }
   hipLaunchKernelGGL(k_rects, dim3(std::max(1u, (E + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, vt, b.rec,
-                     (const uint32_t*)b.dval[b.dsorted], (const uint32_t*)psum, b.counters, b.dkey[0], b.dkey[1]);
+                     (const uint32_t*)b.dval[place ? 0 : b.dsorted], (const uint32_t*)place, b.dval[1],
+                     (const uint32_t*)psum, b.counters, b.dkey[0], b.dkey[1]);
   // item offsets in depth order
   if (!test_entries(b.E, b.total_patches))
-    scan1<false>(PatchCount{b.dkey[0], b.dkey[1]},
+    scan1<false, false>(PatchCount{b.dkey[0], b.dkey[1]},
                  StoreOffset{b.poff, b.blk_start, b.nblk_start, (int64_t)kBlock * sort_items(b.pcap)},
                  &b.counters[0], 0u, E, b.E, rs.tickets + kMaxPasses + 1, rs.scan_status + rs.nscan, &b.counters[7],
                  (uint32_t*)nullptr, (uint32_t*)nullptr, &b.counters[3], st);
@@ -1387,7 +1466,7 @@ void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t items_hint, bo
     hipLaunchKernelGGL(k_list_scan, dim3((unsigned)b.total_patches + gz), dim3(kScanThreads), 0, st, vt,
                        (const uint2*)b.ranges, (const uint32_t*)b.counters, cap, list_chunk, table, b.tile_order,
                        b.order_state, (const uint32_t*)b.tiles, b.E, b.g2d);
-    scan1<false>(CountVal{b.tile_order}, StoreRange{b.ranges}, nullptr, T, T, T, rs.tickets,
+    scan1<false, false>(CountVal{b.tile_order}, StoreRange{b.ranges}, nullptr, T, T, T, rs.tickets,
                  reinterpret_cast<uint64_t*>(rs.tickets + kGhStride), (uint32_t*)nullptr, (uint32_t*)nullptr,
                  (uint32_t*)nullptr, &b.counters[3], st);
   };
@@ -1467,7 +1546,7 @@ void launch_count_scan(const uint32_t* cnt, int64_t n, uint32_t* off, uint32_t* 
   const int64_t words = chunk_scan_words(n);
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, state, words);
   const uint32_t N = (uint32_t)n;
-  scan1<false>(CountVal{cnt}, CountOffset{off}, nullptr, N, N, n, state, reinterpret_cast<uint64_t*>(state + 2), total,
+  scan1<false, false>(CountVal{cnt}, CountOffset{off}, nullptr, N, N, n, state, reinterpret_cast<uint64_t*>(state + 2), total,
                (uint32_t*)nullptr, (uint32_t*)nullptr, err, st);
 }
 

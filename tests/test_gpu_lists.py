@@ -1,7 +1,8 @@
 """The tiles' lists at the edges of how they are built: patches of 8 x 8 tiles
 (images of one, a little more and less), chunks of the tested entries (256 and
 1,024), and the items sorted by patch in one and in two radix passes, growing
-and at a fixed capacity -- against the oracle's sorted pairs, bit for bit."""
+and at a fixed capacity, with the depths sorted by counting (up to 20,480
+entries) and by radix passes -- against the oracle's sorted pairs, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +19,7 @@ pytestmark = pytest.mark.gpu
     ([(128, 128)], 1, 30.0, (16, 16)), ([(128, 128)], 255, 30.0, (16, 16)), ([(128, 128)], 257, 30.0, (32, 8)),
     ([(129, 127)], 1024, 30.0, (16, 16)), ([(127, 129), (16, 16), (144, 130)], 1025, 60.0, (16, 16)),
     ([(1000, 1000)], 16000, 10.0, (16, 16)), ([(1000, 1000)], 17000, 10.0, (16, 16)),  # 256 and 1,024 per workgroup
-    ([(1000, 1000)], 17000, 10.0, (8, 32)), ([(1700, 40)], 40000, 25.0, (16, 16)),
+    ([(1000, 1000)], 20481, 10.0, (8, 32)), ([(1700, 40)], 20480, 25.0, (16, 16)),
     ([(512, 512)] * 16, 8500, 12.0, (16, 16)),             # sorted items, 256 patches
     ([(640, 512), (200, 500)] * 8, 12000, 12.0, (16, 16)),  # two passes
     ([(640, 512), (200, 500)] * 8, 12000, 300.0, (32, 8))])
