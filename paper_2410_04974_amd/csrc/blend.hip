@@ -605,13 +605,15 @@ struct BwdWave {
   float dC[3];          // dL/dC (lane = pixel)
   float dcA[4];         // dL/dC as the pixel operand of dL/dC . c
   float one[4];         // 1 in the lanes 4 i + j
+  uint32_t qlast[4];    // per quad of pixels: list positions from here on no pixel takes,
+  uint32_t qmin;        // list positions before here no pixel compares
 };
 
 // A group's Gaussian in this lane, and its sums over the pixels of the row.
 struct BwdGauss {
   float cA;
   float dx[8];                // pixel columns
-  float bdy[2], cdy[2];       // the exponent's terms of the row's two pixel lines
+  float bdy[2], cdy[2];       // the exponent's terms of the row's two pixel lines (4 apart)
   uint32_t pos;               // list position
   float s0[2], s1[2], s2[2];  // per pixel line: sums of w, w dx, w dx^2 (w = dL/d(exponent))
   float col[3];               // colour gradient
@@ -673,15 +675,18 @@ __device__ __forceinline__ void bwd_steps(BwdWave& W, BwdGauss& G, float col) {
   }
 }
 
+// pos0: the group's first list position; a 4 x 4 quad of pixels that all ended
+// before it is left out (16 uneven views of 500k Gaussians 3410 -> 3325 us, one
+// 800x800 view of 300k 169 -> 166; a form chosen for each quad: 3450, 174).
 template <BwdForm FORM>
-__device__ __forceinline__ void bwd_group(BwdWave& W, BwdGauss& G, float col) {
+__device__ __forceinline__ void bwd_group(BwdWave& W, BwdGauss& G, float col, uint32_t pos0) {
   // keeps the forms' exponents apart: formed ahead of the choice between
   // them, all sixteen would be held in registers
   asm volatile("" : "+v"(G.cA));
-  bwd_steps<0, FORM>(W, G, col);
-  bwd_steps<1, FORM>(W, G, col);
-  bwd_steps<2, FORM>(W, G, col);
-  bwd_steps<3, FORM>(W, G, col);
+  if (FORM == kFree || pos0 < W.qlast[0]) bwd_steps<0, FORM>(W, G, col);
+  if (FORM == kFree || pos0 < W.qlast[1]) bwd_steps<1, FORM>(W, G, col);
+  if (FORM == kFree || pos0 < W.qlast[2]) bwd_steps<2, FORM>(W, G, col);
+  if (FORM == kFree || pos0 < W.qlast[3]) bwd_steps<3, FORM>(W, G, col);
 }
 
 // One work item = one chunk of `chunk` list positions of one tile, walked
@@ -721,10 +726,12 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
   const int local = tile - vd.tile_base;
   const int tx = local % vd.ntx, ty = local / vd.ntx;
   const int wv = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  // a pixel per lane for the walk's state: lane 16 row + s holds that of step s,
+  // so that steps 4 K .. 4 K + 3 of the four rows are a 4 x 4 quad of the block
   const int gj = l & 15, row = l >> 4;
   const float ox = (float)(tx * TW) + 0.5f, oy = (float)(ty * TileMap<TW>::TH) + 0.5f;
   const int px = tx * TW + TileMap<TW>::bx(wv) + (l & 7);
-  const int py = ty * TileMap<TW>::TH + TileMap<TW>::by(wv) + (l >> 3);
+  const int py = ty * TileMap<TW>::TH + TileMap<TW>::by(wv) + 4 * (gj >> 3) + row;
   const bool inside = px < vd.W && py < vd.H;
   // pixel centres of the wavefront's block: its columns, and the row's first line
   float fx[8];
@@ -732,7 +739,7 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
   for (int k = 0; k < 8; k++)
     fx[k] = __uint_as_float(__builtin_amdgcn_readfirstlane(
         __float_as_uint((float)(tx * TW + TileMap<TW>::bx(wv) + k) + 0.5f)));
-  const float by0 = (float)(ty * TileMap<TW>::TH + TileMap<TW>::by(wv) + 2 * row) + 0.5f;
+  const float by0 = (float)(ty * TileMap<TW>::TH + TileMap<TW>::by(wv) + row) + 0.5f;
 
   float Tf = 0.f, dC0 = 0.f, dC1 = 0.f, dC2 = 0.f;
   uint32_t last = 0;
@@ -779,7 +786,7 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
     // the pixel takes Gaussians past this chunk: resume from the state saved
     // where the next chunk begins (otherwise its final state is that state)
     const int64_t slot = ((int64_t)rg.x + cstart + chunk) >> bs.chunk_shift;
-    const float4 st = slot < bs.nbound ? bs.bound[slot * kBlock + threadIdx.x] : make_float4(1.f, 0.f, 0.f, 0.f);
+    const float4 st = slot < bs.nbound ? bs.bound[slot * kBlock + wv * 64 + (4 * (gj >> 3) + row) * 8 + (l & 7)] : make_float4(1.f, 0.f, 0.f, 0.f);
     W.T = st.x;
     S0 += st.y;
     S1 += st.z;
@@ -791,8 +798,12 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
   // that took every Gaussian that reaches 1/255 there, so only the others
   // compare list positions.
   W.lastcmp = (Tf > 0.0101f || !inside) ? 0xFFFFFFFFu : last;
-  uint32_t minlast = ~wave_max(~W.lastcmp);
-  minlast = __builtin_amdgcn_readfirstlane(minlast);
+  W.qmin = __builtin_amdgcn_readfirstlane(~wave_max(~W.lastcmp));
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    const bool mine = gj >> 2 == k;
+    W.qlast[k] = __builtin_amdgcn_readfirstlane(wave_max(mine ? last : 0u));
+  }
   const uint32_t cend = min(cstart + chunk, maxlast);
   const float kq = -0.5f * kLog2e;
 
@@ -800,13 +811,13 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
     const uint32_t b0 = (bend - (rg.x + cstart) > (uint32_t)batch) ? bend - batch : rg.x + cstart;
     const uint32_t nb = bend - b0;
     const uint32_t wn = stage_batch<TW, MAXB>(L, rec, pval, b0, nb, ox, oy);
-    const uint32_t pos0 = b0 - rg.x;
+    const uint32_t posb = b0 - rg.x;
     for (int g = (int)((wn + 15) >> 4) - 1; g >= 0; g--) {
       // lane j takes list slot 16 g + j; past the list a Gaussian that no pixel takes
       const uint32_t i = 16 * (uint32_t)g + gj;
       const uint32_t slot = L.list[wv][min(i, wn - 1)];
       BwdGauss G;
-      G.pos = pos0 + slot;
+      G.pos = posb + slot;
       if (__builtin_amdgcn_readfirstlane(G.pos) >= wlast) continue;  // behind every pixel's last
       const Staged& sr = L.rec[slot];
       const float4 A = sr.a;
@@ -819,18 +830,19 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
       float dy[2];
 #pragma unroll
       for (int h = 0; h < 2; h++) {
-        dy[h] = (by0 + (float)h) - A.y;
+        dy[h] = (by0 + 4.f * (float)h) - A.y;
         G.bdy[h] = __fmul_rn(A.w, dy[h]);
         G.cdy[h] = __fmaf_rn(__fmul_rn(B.x, dy[h]), dy[h], B.y);
         G.s0[h] = G.s1[h] = G.s2[h] = 0.f;
       }
       G.col[0] = G.col[1] = G.col[2] = 0.f;
+      const uint32_t pos0 = __builtin_amdgcn_readfirstlane(G.pos), pos1 = __builtin_amdgcn_readlane(G.pos, 15);
       if (__ballot(clamps))
-        bwd_group<kExact>(W, G, col);
-      else if (__ballot(G.pos >= minlast))
-        bwd_group<kStops>(W, G, col);
+        bwd_group<kExact>(W, G, col, pos0);
+      else if (pos1 >= W.qmin)
+        bwd_group<kStops>(W, G, col, pos0);
       else
-        bwd_group<kFree>(W, G, col);
+        bwd_group<kFree>(W, G, col, pos0);
       // the moments of w about the Gaussian's centre and the colour gradient,
       // summed over the four rows (halving exchanges) and added in LDS
       const float v[kG2D] = {G.s1[0] + G.s1[1],
