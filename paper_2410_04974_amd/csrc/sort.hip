@@ -985,7 +985,7 @@ __device__ __forceinline__ void order_tiles(const uint2* __restrict__ ranges, ui
 // dozen neighbours or so at a time.  Radix sorting the pairs (8 bytes) by tile
 // moved each five times, 124 vector instructions per 64 and pass, and bound the
 // stage by memory: 16 views of 500k Gaussians, 144M pairs, 3,350 us for the
-// whole stage then and 1,080 now (342 of them the writes, 1.7 TB/s: runs of
+// whole stage then and 1,035 now (283 of them the writes, 2.0 TB/s: runs of
 // 50 bytes); one 1408x1408 view of 175k, 4.9M pairs, 195 and 110; one 800x800
 // view of 300k, 3.4M pairs, 164 and 120.
 __device__ __forceinline__ uint32_t readlane(uint32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
@@ -1005,14 +1005,31 @@ __device__ __forceinline__ uint32_t patch_bits(uint32_t x0, uint32_t x1, uint32_
   return ((2u << x1) - (1u << x0)) | ((2u << y1) - (1u << y0)) << 8;
 }
 
-// Up to 64 entries of a patch, in order by lane (bits 0: none), and its ROWS
-// rows of tiles from row0 on: lane t's n, t < 8 ROWS, moves on by the entries of
-// the t-th of these tiles, and with WRITE entry e of the lane goes to out[n ...]
-// of those it covers.  False if the output were exceeded (never for consistent
-// counts).
-template <bool WRITE, int ROWS>
-__device__ __forceinline__ bool list_entries(uint32_t bits, uint32_t e, int row0, uint32_t& n, uint32_t pcap,
-                                             uint32_t* __restrict__ out) {
+// Up to 64 entries of a patch, in order by lane (bits 0: none): lane t gets the
+// mask of those that cover the patch's tile t.
+__device__ __forceinline__ uint2 tile_masks(uint32_t bits) {
+  const int lane = (int)__lane_id();
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int q = 0; q < 16; q++) put_lane(lo, hi, __ballot((bits >> q) & 1u), q);
+  const int x = lane & 7, y = 8 + (lane >> 3);
+  return make_uint2(__shfl(lo, x, 64) & __shfl(lo, y, 64), __shfl(hi, x, 64) & __shfl(hi, y, 64));
+}
+__device__ __forceinline__ uint32_t popc(uint2 m) { return (uint32_t)(__popc(m.x) + __popc(m.y)); }
+
+// Writes e of the lanes in a tile's mask to out[at ...].
+__device__ __forceinline__ void write_tile(uint64_t m, uint32_t e, uint32_t at, uint32_t* __restrict__ out) {
+  const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, at));
+  if (__builtin_amdgcn_inverse_ballot_w64(m))
+    *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(out) + (uint64_t)(uint32_t)(4 * to)) = e;
+}
+
+// The same for two rows of tiles, with the writes: lane t's n, t < 16, moves on by
+// the entries of the t-th of these tiles, and entry e of the lane goes to
+// out[n ...] of those it covers.  False if the output were exceeded (never for
+// consistent counts).
+__device__ __forceinline__ bool write_rows(uint32_t bits, uint32_t e, int row0, uint32_t& n, uint32_t pcap,
+                                           uint32_t* __restrict__ out) {
   const int lane = (int)__lane_id();
   uint64_t col[8];
   uint32_t lo = 0, hi = 0;
@@ -1023,25 +1040,16 @@ __device__ __forceinline__ bool list_entries(uint32_t bits, uint32_t e, int row0
   }
   const uint32_t rbits = bits >> (8 + row0);
 #pragma unroll
-  for (int r = 0; r < ROWS; r++) put_lane(lo, hi, __ballot((rbits >> r) & 1u), 8 + r);
-  const int x = lane & 7, y = 8 + ((lane >> 3) & (ROWS - 1));
-  const uint32_t cnt = (uint32_t)(__popc(__shfl(lo, x, 64) & __shfl(lo, y, 64)) +
-                                  __popc(__shfl(hi, x, 64) & __shfl(hi, y, 64)));
-  if constexpr (WRITE) {
-    if (__ballot((uint64_t)n + cnt > pcap)) return false;
+  for (int r = 0; r < 2; r++) put_lane(lo, hi, __ballot((rbits >> r) & 1u), 8 + r);
+  const int x = lane & 7, y = 8 + ((lane >> 3) & 1);
+  const uint32_t cnt = popc(make_uint2(__shfl(lo, x, 64) & __shfl(lo, y, 64), __shfl(hi, x, 64) & __shfl(hi, y, 64)));
+  if (__ballot((uint64_t)n + cnt > pcap)) return false;
 #pragma unroll 1
-    for (int r = 0; r < ROWS; r++) {
-      const uint64_t row = (uint64_t)readlane(hi, 8 + r) << 32 | readlane(lo, 8 + r);
-      if (row == 0) continue;
+  for (int r = 0; r < 2; r++) {
+    const uint64_t row = (uint64_t)readlane(hi, 8 + r) << 32 | readlane(lo, 8 + r);
+    if (row == 0) continue;
 #pragma unroll
-      for (int c = 0; c < 8; c++) {
-        const uint64_t m = col[c] & row;
-        const uint32_t at = __builtin_amdgcn_mbcnt_hi(
-            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, readlane(n, 8 * r + c)));
-        if (__builtin_amdgcn_inverse_ballot_w64(m))
-          *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(out) + (uint64_t)(uint32_t)(4 * at)) = e;
-      }
-    }
+    for (int c = 0; c < 8; c++) write_tile(col[c] & row, e, readlane(n, 8 * r + c), out);
   }
   n += cnt;
   return true;
@@ -1079,21 +1087,69 @@ constexpr int kListWG = 8192;  // workgroups at most: each takes further chunks
 // an id past the last.
 __device__ __forceinline__ uint32_t xcd_unit(uint32_t b, uint32_t units) { return (b & 7u) * ((units + 7u) / 8u) + (b >> 3); }
 
-template <bool WRITE>
+// The patch_bits of an item's key.
+__device__ __forceinline__ uint32_t item_bits(uint32_t key) {
+  const uint32_t r = key >> 20;
+  return patch_bits(r & 7, (r >> 3) & 7, (r >> 6) & 7, r >> 9);
+}
+
+__global__ void __launch_bounds__(kBlock) k_item_counts(const uint32_t* __restrict__ key,
+                                                        const uint32_t* __restrict__ counters, uint32_t pcap,
+                                                        uint32_t* __restrict__ table, uint2* __restrict__ ranges) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (overflowed(counters, pcap)) return;
+  const uint32_t S = counters[7];
+  const uint32_t nchunk = (S + kListItems - 1) / kListItems;
+  for (uint32_t c = blockIdx.x * kWaves + wv; c < nchunk; c += gridDim.x * kWaves) {
+    const uint32_t i0 = c * kListItems, i1 = min(i0 + kListItems, S);
+    uint32_t n = 0, patch = i0 > 0 ? key[i0 - 1] & kPatchMask : ~0u;  // goes on from the chunk before
+    bool first = true;
+    uint32_t k = i0 + lane < i1 ? key[i0 + lane] : ~0u;
+    for (uint32_t i = i0; i < i1; i += 64) {
+      const uint32_t in = i + 64 + lane;
+      const uint32_t kn = in < i1 ? key[in] : ~0u;
+      const uint32_t id = k & kPatchMask;
+      uint64_t todo = __ballot(i + lane < i1);
+      while (todo) {
+        const int f = __ffsll((unsigned long long)todo) - 1;
+        const uint32_t p = readlane(id, f);
+        if (first || p != patch) {
+          if (!first) table[(uint64_t)(c + patch) * 64 + lane] = n;
+          if (p != patch && lane == 0) {  // patch ends and p starts here
+            if (patch != ~0u) ranges[patch].y = i + f;
+            ranges[p].x = i + f;
+          }
+          n = 0;
+          patch = p;
+          first = false;
+        }
+        todo &= ~__ballot(id == p);
+        n += popc(tile_masks(id == p ? item_bits(k) : 0u));
+      }
+      k = kn;
+    }
+    table[(uint64_t)(c + patch) * 64 + lane] = n;
+    if (i1 == S && lane == 0) ranges[patch].y = S;
+  }
+}
+
+// A tile's entries of the whole chunk are written one step after the other: step
+// by step over the 64 tiles, the half-written cache lines of all wavefronts did
+// not fit the L2 caches (144M pairs, 4.5M lines: 11.4M line write-backs and
+// 342 us, now 4.9M and 283 us; chunks of 512 items 310 us).
 __global__ void __launch_bounds__(kBlock) k_item_lists(ViewTable vt, const uint32_t* __restrict__ key,
                                                        const uint32_t* __restrict__ val,
                                                        const uint32_t* __restrict__ counters, uint32_t pcap,
-                                                       uint32_t* __restrict__ table, uint2* __restrict__ ranges,
-                                                       uint32_t* __restrict__ out, uint32_t* __restrict__ order_state,
+                                                       const uint32_t* __restrict__ table,
+                                                       const uint2* __restrict__ ranges, uint32_t* __restrict__ out,
+                                                       uint32_t* __restrict__ order_state,
                                                        uint32_t* __restrict__ order) {
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t first_wg = 0;
-  if (WRITE) {  // the first workgroups order the tiles
-    first_wg = order_wgs((uint32_t)vt.total_tiles);
-    if (blockIdx.x < first_wg) {
-      order_tiles(ranges, (uint32_t)vt.total_tiles, blockIdx.x, order_state, order);
-      return;
-    }
+  // the first workgroups order the tiles
+  const uint32_t first_wg = order_wgs((uint32_t)vt.total_tiles);
+  if (blockIdx.x < first_wg) {
+    order_tiles(ranges, (uint32_t)vt.total_tiles, blockIdx.x, order_state, order);
+    return;
   }
   if (overflowed(counters, pcap)) return;
   const uint32_t S = counters[7];
@@ -1103,51 +1159,51 @@ __global__ void __launch_bounds__(kBlock) k_item_lists(ViewTable vt, const uint3
     const uint32_t u = xcd_unit(b, units);
     const uint32_t c = u * kWaves + wv;
     if (u >= units || c >= nchunk) continue;
-    const uint32_t i0 = c * kListItems, i1 = min(i0 + kListItems, S);
-    uint32_t patch = ~0u, n = 0;  // WRITE: where tile `lane`'s next entry goes; else its entries so far
-    if (!WRITE && i0 > 0) patch = key[i0 - 1] & kPatchMask;  // goes on from the chunk before
-    bool first = true;
-    uint32_t k = i0 + lane < i1 ? key[i0 + lane] : ~0u;
-    uint32_t e = WRITE && i0 + lane < i1 ? val[i0 + lane] : 0u;
-    for (uint32_t i = i0; i < i1; i += 64) {
-      const uint32_t in = i + 64 + lane;
-      uint32_t kn = in < i1 ? key[in] : ~0u;
-      uint32_t en = WRITE && in < i1 ? val[in] : 0u;
-      arrived(e);
-      const uint32_t id = k & kPatchMask;
-      uint64_t todo = __ballot(i + lane < i1);
-      while (todo) {
-        const int f = __ffsll((unsigned long long)todo) - 1;
-        const uint32_t p = readlane(id, f);
-        if (first || p != patch) {
-          if constexpr (WRITE) {
-            const int tile = patch_tile(vt, p, lane);
-            n = table[(uint64_t)(c + p) * 64 + lane] + (tile >= 0 ? ranges[tile].x : 0u);
-            arrived(n);
-          } else {
-            if (!first) table[(uint64_t)(c + patch) * 64 + lane] = n;
-            if (p != patch) {  // patch ends and p starts here
-              if (lane == 0) {
-                if (patch != ~0u) ranges[patch].y = i + f;
-                ranges[p].x = i + f;
-              }
-            }
-            n = 0;
-          }
-          patch = p;
-          first = false;
-        }
-        todo &= ~__ballot(id == p);
-        const uint32_t r = k >> 20;
-        const uint32_t bits = id == p ? patch_bits(r & 7, (r >> 3) & 7, (r >> 6) & 7, r >> 9) : 0u;
-        if (!list_entries<WRITE, 8>(bits, e, 0, n, pcap, out)) return;
-      }
-      k = kn;
-      e = en;
+    const uint32_t i0 = c * kListItems + lane;
+    uint32_t k[kListSteps], e[kListSteps];
+#pragma unroll
+    for (int s = 0; s < kListSteps; s++) {
+      const bool in = i0 + 64 * s < S;
+      k[s] = in ? key[i0 + 64 * s] : ~0u;
+      e[s] = in ? val[i0 + 64 * s] : 0u;
     }
-    if (!WRITE) {
-      table[(uint64_t)(c + patch) * 64 + lane] = n;
-      if (i1 == S && lane == 0) ranges[patch].y = S;
+    const uint32_t plast = key[min(c * kListItems + kListItems, S) - 1] & kPatchMask;
+    for (uint32_t p = readlane(k[0], 0) & kPatchMask;;) {
+      const int tile = patch_tile(vt, p, lane);
+      uint32_t n = table[(uint64_t)(c + p) * 64 + lane] + (tile >= 0 ? ranges[tile].x : 0u);
+      uint2 m[kListSteps];
+      uint32_t cnt = 0;
+#pragma unroll
+      for (int s = 0; s < kListSteps; s++) {
+        const bool mine = (k[s] & kPatchMask) == p;
+        m[s] = make_uint2(0u, 0u);
+        if (__ballot(mine)) m[s] = tile_masks(mine ? item_bits(k[s]) : 0u);
+        cnt += popc(m[s]);
+      }
+      if (__ballot((uint64_t)n + cnt > pcap)) return;  // never for consistent counts; guards the buffer
+#pragma unroll
+      for (int s = 0; s < kListSteps; s++) arrived(e[s]);
+      arrived(n);
+      for (uint64_t todo = __ballot(cnt > 0); todo; todo &= todo - 1) {
+        const int t = __ffsll((unsigned long long)todo) - 1;
+        uint32_t at = readlane(n, t);
+#pragma unroll
+        for (int s = 0; s < kListSteps; s++) {
+          const uint64_t mt = (uint64_t)readlane(m[s].y, t) << 32 | readlane(m[s].x, t);
+          write_tile(mt, e[s], at, out);
+          at += (uint32_t)__popcll(mt);
+        }
+      }
+      if (p == plast) break;
+      // the next patch among the chunk's items
+      uint32_t next = ~0u;
+#pragma unroll
+      for (int s = kListSteps - 1; s >= 0; s--) {
+        const uint64_t after = __ballot((k[s] & kPatchMask) > p && i0 + 64 * s < S);
+        if (after) next = readlane(k[s], __ffsll((unsigned long long)after) - 1) & kPatchMask;
+      }
+      if (next == ~0u) break;
+      p = next;
     }
   }
 }
@@ -1241,11 +1297,11 @@ __global__ void __launch_bounds__(kBlock) k_entry_lists(ViewTable vt, const uint
     arrived(n);
     for (uint32_t k = 0; k < nh; k += 64) {
       const bool in = k + lane < nh;
-      if (!list_entries<true, 2>(in ? s_bits[k + lane] : 0u, in ? s_e[k + lane] : 0u, 2 * wv, n, pcap, out)) return;
+      if (!write_rows(in ? s_bits[k + lane] : 0u, in ? s_e[k + lane] : 0u, 2 * wv, n, pcap, out)) return;
     }
   } else {
     for (uint32_t k = 64 * wv; k < nh; k += kBlock)
-      list_entries<false, 8>(k + lane < nh ? s_bits[k + lane] : 0u, 0u, 0, n, pcap, out);
+      n += popc(tile_masks(k + lane < nh ? s_bits[k + lane] : 0u));
     s_n[wv][lane] = n;
     __syncthreads();
     if (wv == 0) row[lane] = s_n[0][lane] + s_n[1][lane] + s_n[2][lane] + s_n[3][lane];
@@ -1516,13 +1572,12 @@ void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t items_hint, bo
     const uint32_t* const k = b.pkey[cur];
     const uint32_t* const v = b.pval[cur];
     if (units)
-      hipLaunchKernelGGL(k_item_lists<false>, dim3(grid), dim3(kBlock), 0, st, vt, k, v, (const uint32_t*)b.counters,
-                         cap, table, b.ranges, b.pval[cur ^ 1], b.order_state, b.tile_order);
+      hipLaunchKernelGGL(k_item_counts, dim3(grid), dim3(kBlock), 0, st, k, (const uint32_t*)b.counters, cap, table,
+                         b.ranges);
     ranges_of(0);
     if (grid + ow)
-      hipLaunchKernelGGL(k_item_lists<true>, dim3(grid + ow), dim3(kBlock), 0, st, vt, k, v,
-                         (const uint32_t*)b.counters, cap, table, b.ranges, b.pval[cur ^ 1], b.order_state,
-                         b.tile_order);
+      hipLaunchKernelGGL(k_item_lists, dim3(grid + ow), dim3(kBlock), 0, st, vt, k, v, (const uint32_t*)b.counters, cap,
+                         (const uint32_t*)table, (const uint2*)b.ranges, b.pval[cur ^ 1], b.order_state, b.tile_order);
     cur ^= 1;
   }
   b.psorted = cur;
