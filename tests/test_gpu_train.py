@@ -241,3 +241,19 @@ def test_training_with_dssim_lowers_the_loss():
     losses = [float(tr.step([cam], tgt)) for _ in range(15)]
     print("l1+dssim training", losses[0], "->", losses[-1], flush=True)
     assert losses[-1] < 0.8 * losses[0]
+
+
+@pytest.mark.parametrize("size", [(1, 1), (5, 100), (15, 31), (16, 32), (17, 33), (33, 65)])
+def test_l1_dssim_at_the_edges_of_its_tiles(size):
+    """One image around the 32x16 tiles of the SSIM kernels, whole and cut, with
+    the bars of the comparison above."""
+    rng = np.random.default_rng(13)
+    img = rng.random((3, *size)).astype(np.float32)
+    tgt = np.clip(img + rng.normal(0, 0.1, img.shape), 0, 1).astype(np.float32)
+    r = G.renderer()
+    di, dt = torch.from_numpy(img).to(G.DEV), torch.from_numpy(tgt).to(G.DEV)
+    dl, loss = torch.empty_like(di), torch.zeros(1, device=G.DEV)
+    r.ctx.l1_dssim_loss([di], [dt], [dl], loss, lambda_dssim=0.2)
+    ref_loss, ref_grads = oracle.l1_dssim_loss([img], [tgt], lam=0.2)
+    assert abs(float(loss) - ref_loss) <= 1e-5 * ref_loss
+    assert np.abs(dl.cpu().numpy() - ref_grads[0]).max() <= 1e-4 * np.abs(ref_grads[0]).max()
