@@ -257,3 +257,32 @@ def test_l1_dssim_at_the_edges_of_its_tiles(size):
     ref_loss, ref_grads = oracle.l1_dssim_loss([img], [tgt], lam=0.2)
     assert abs(float(loss) - ref_loss) <= 1e-5 * ref_loss
     assert np.abs(dl.cpu().numpy() - ref_grads[0]).max() <= 1e-4 * np.abs(ref_grads[0]).max()
+
+
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 1021, 1024, 1027])
+def test_adam_rows_of_any_length(n, aligned):
+    """Rows whose ends cut its groups of four, and arrays off their alignment,
+    with the bars of the comparison above; what lies before and behind the
+    arrays stays as it was."""
+    from paper_2410_04974_amd import adam
+    rng = np.random.default_rng(n)
+    off = 0 if aligned else 1
+
+    def arr(a):
+        b = torch.full((76 * n + 16,), 7.0, device=G.DEV)
+        view = b[4 + off:4 + off + 76 * n].view(76, n)
+        view.copy_(torch.from_numpy(a))
+        return b, view
+    p, g, m = (rng.normal(size=(76, n)).astype(np.float32) for _ in range(3))
+    v = rng.random(size=(76, n)).astype(np.float32)
+    bufs, views = zip(*(arr(a) for a in (p, g, m, v)))
+    adam(*views, LR, 3)
+    torch.cuda.synchronize()
+    ref = oracle.adam_step(p.astype(np.float64), g, m.astype(np.float64), v.astype(np.float64), 3,
+                           [float(np.float32(x)) for x in LR], b1=float(np.float32(0.9)), b2=float(np.float32(0.999)),
+                           eps=float(np.float32(1e-15)))
+    for got, want, atol in zip((views[0], views[2], views[3]), ref, (1e-6, 1e-7, 1e-9)):
+        assert np.allclose(got.cpu().numpy(), want, rtol=1e-5, atol=atol)
+    for b in bufs:
+        assert bool((b[:4 + off] == 7.0).all()) and bool((b[4 + off + 76 * n:] == 7.0).all())
