@@ -112,7 +112,8 @@ struct sixdgs_ctx {
   DevBuf<float> g2d, l1_partial, ssim_maps, ssim_partial;
   // scratch
   DevBuf<uint32_t> rstate, blk_start, counters, tile_order, order_state;
-  uint32_t* host_counters = nullptr;  // pinned
+  uint64_t* host_words = nullptr;  // pinned: counts that kernels hand to the host (HostCount)
+  uint32_t host_seq = 0;
   // state of the last forward
   bool have_fwd = false;
   float* bin_g2d = nullptr;  // the gradient accumulators the binning clears (training forwards)
@@ -184,6 +185,7 @@ sixdgs_status fail(sixdgs_ctx* c, sixdgs_status st, const std::string& msg) {
 // timeout flag, [4] backward work items, [5] density-control outputs, [6] the
 // fused backward + Adam's finished workgroups (zero between launches)
 constexpr int kCounters = 8;
+constexpr int kHostWords = 2;
 
 // Bound on entries and pairs: the radix sort's look-back words hold 30-bit counts.
 constexpr int64_t kMaxItems = (1ll << 30) - 1;
@@ -422,29 +424,58 @@ sixdgs_status prepare_binning(sixdgs_ctx* c, int64_t E) {
   return SIXDGS_OK;
 }
 
+// Word k for this call's kernels to hand a count in (after next_seq).
+HostCount host_count(sixdgs_ctx* c, int k) { return HostCount{c->host_words + k, c->host_seq}; }
+void next_seq(sixdgs_ctx* c) {
+  if (++c->host_seq == 0) c->host_seq = 1;  // the words start as 0
+}
+
+// Waits until a kernel on st has published h's count.  Looks at the word for up
+// to about 2 ms, then waits for the stream: a copy and a stream
+// synchronisation, as every call took, are 10-15 us longer than the store.
+bool wait_count(const HostCount& h, hipStream_t st, int64_t& count) {
+  for (int spin = 0; spin < (1 << 16); spin++) {
+    const uint64_t v = __atomic_load_n(h.word, __ATOMIC_RELAXED);
+    if ((uint32_t)(v >> 32) == h.seq) {
+      count = (uint32_t)v;
+      return true;
+    }
+    __builtin_ia32_pause();
+  }
+  if (hipStreamSynchronize(st) != hipSuccess) return false;
+  const uint64_t v = __atomic_load_n(h.word, __ATOMIC_RELAXED);
+  count = (uint32_t)v;
+  return (uint32_t)(v >> 32) == h.seq;
+}
+
 // Integer stage after the records and tile counts of E entries exist
 // (prepare_binning first; prepped: bin_prep was done by the launch before).
 sixdgs_status run_binning(sixdgs_ctx* c, int64_t E, bool prepped, hipStream_t st) {
   const bool fixed = c->s.pair_capacity > 0;
   Timer t(c, SIXDGS_K_SORT, st);
+  c->sb.host_pairs = c->sb.host_items = HostCount{};
+  if (!fixed) {
+    next_seq(c);
+    c->sb.host_pairs = host_count(c, 0);
+    if (sorts_items(c->sb)) c->sb.host_items = host_count(c, 1);
+  }
   launch_bin_count(c->sb, c->vt, prepped, st);
   int64_t hint = c->sb.pcap;
   bool regrown = false;
   if (!fixed) {
     // read the pair count back, then size the pair buffers exactly (with slack for the next call)
-    if (hipMemcpyAsync(c->host_counters, c->counters.p, kCounters * sizeof(uint32_t), hipMemcpyDeviceToHost, st) !=
-            hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
+    int64_t P = 0, S = 0;
+    if (!wait_count(c->sb.host_pairs, st, P) || (c->sb.host_items.word && !wait_count(c->sb.host_items, st, S)))
       return fail(c, SIXDGS_ERR_HIP, "pair count read-back failed");
-    const int64_t P = c->host_counters[1];
     if (P > kMaxItems) return fail(c, SIXDGS_ERR_CAPACITY, "more than 2^30 - 1 pairs");
     if (P > c->sb.pcap) {
+      if (hipStreamSynchronize(st) != hipSuccess) return fail(c, SIXDGS_ERR_HIP, "stream synchronisation failed");
       if (!ensure_pairs(c, P, 1.25)) return fail(c, SIXDGS_ERR_OOM, "pair buffers");
       if (!ensure_scratch(c, E, c->pkey0.cap)) return fail(c, SIXDGS_ERR_OOM, "sort scratch");
       fill_sort_buffers(c, E);  // keeps dsorted: the depth-sorted entries are untouched
       regrown = true;
     }
-    hint = c->host_counters[7];
+    hint = S;
   }
   launch_bin_emit(c->sb, c->vt, hint, regrown, st);
   return check_launch(c, "binning");
@@ -621,10 +652,11 @@ sixdgs_status sixdgs_create(sixdgs_ctx** out, const sixdgs_settings* s) {
   sixdgs_ctx* c = new (std::nothrow) sixdgs_ctx();
   if (!c) return SIXDGS_ERR_OOM;
   c->s = *s;
-  if (hipHostMalloc((void**)&c->host_counters, kCounters * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void**)&c->host_words, kHostWords * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
     delete c;
     return SIXDGS_ERR_HIP;
   }
+  for (int k = 0; k < kHostWords; k++) c->host_words[k] = 0;
   set_debug(c, (s->flags & SIXDGS_FLAG_DEBUG) != 0);
   if (!init_counters(c)) {
     sixdgs_destroy(c);
@@ -640,7 +672,7 @@ void sixdgs_destroy(sixdgs_ctx* c) {
   collect_timing(c);
   for (hipEvent_t e : c->free_events) (void)hipEventDestroy(e);
   for_each_buf(c, [](auto& b, const char*) { b.release(); });
-  if (c->host_counters) (void)hipHostFree(c->host_counters);
+  if (c->host_words) (void)hipHostFree(c->host_words);
   delete c;
 }
 
@@ -1064,14 +1096,13 @@ static sixdgs_status densify_plan_body(sixdgs_ctx* c, const float* params, int64
   if (!c->dens_dec.ensure(n1) || !c->dens_cnt.ensure(n1) || !c->dens_off.ensure(n1) ||
       !c->dens_state.ensure(chunk_scan_words(n1)))
     return fail(c, SIXDGS_ERR_OOM, "density plan buffers");
+  next_seq(c);
+  const HostCount host = host_count(c, 0);
   launch_density_plan(params, n, stats, *d, c->dens_dec.p, c->dens_cnt.p, st);
-  launch_count_scan(c->dens_cnt.p, n, c->dens_off.p, c->counters.p + 5, c->dens_state.p, c->counters.p + 3, st);
-  uint32_t total = 0;
-  if (hipMemcpyAsync(c->host_counters, c->counters.p + 5, sizeof(uint32_t), hipMemcpyDeviceToHost, st) !=
-          hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess)
-    return fail(c, SIXDGS_ERR_HIP, "density plan read-back failed");
-  total = c->host_counters[0];
+  launch_count_scan(c->dens_cnt.p, n, c->dens_off.p, c->counters.p + 5, host, c->dens_state.p,
+                    c->counters.p + 3, st);
+  int64_t total = 0;
+  if (!wait_count(host, st, total)) return fail(c, SIXDGS_ERR_HIP, "density plan read-back failed");
   c->dens_params = params;
   c->dens_n = n;
   c->dens_total = total;

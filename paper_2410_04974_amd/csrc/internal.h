@@ -166,6 +166,17 @@ void launch_preprocess_bwd_adam(float* params, int64_t n, const ViewTable& vt, c
 // sort.hip -- the integer stage
 constexpr int kMaxPasses = 4;  // radix passes of at most 8 bits over a 32-bit key
 
+// Where a kernel hands a count to the waiting host: a pinned word that takes
+// (seq << 32 | count) in one store, or no word.
+struct HostCount {
+  uint64_t* word;
+  uint32_t seq;
+};
+__device__ __forceinline__ void publish(const HostCount& h, uint32_t count) {
+  if (h.word)
+    __hip_atomic_store(h.word, (uint64_t)h.seq << 32 | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 struct SortBuffers {
   // entries
   int64_t E;
@@ -192,6 +203,7 @@ struct SortBuffers {
   uint32_t* order_state;   // [order_state_words()] bucket counts and cursors of the tile order
   uint32_t* n_items;       // the backward work-item count, zeroed here and counted by the forward
   uint32_t* counters;      // [0] binned entries, [1] pairs, [2] overflow flag, [3] sort look-back timeout, [7] sorted items
+  HostCount host_pairs, host_items;  // for the host's copies of counters[1] and [7]
   // where the sorted results ended up (index into the ping-pong pairs)
   int dsorted;
   int psorted;  // pval[psorted] holds the pairs' entries
@@ -201,6 +213,8 @@ int64_t sort_state_words(int64_t bound, bool pairs);
 int64_t list_state_words(int64_t E, int64_t total_tiles, int64_t total_patches);
 int64_t sort_block_starts(int64_t pcap);
 int64_t order_state_words();
+// Whether items are sorted (else there are none and counters[7] is 0).
+bool sorts_items(const SortBuffers& b);
 // The preparation of the integer stage over b (for launch_preprocess).
 BinPrep bin_prep(const SortBuffers& b);
 // Stage 1: compaction of binned entries and their depth sort, then their
@@ -260,7 +274,7 @@ void launch_blend_bwd(const ViewTable& vt, const DevSettings& s, const Rec* rec,
 int64_t chunk_scan_words(int64_t n);
 // sort.hip: exclusive scan of n counts into off, the sum into *total (device);
 // `state` holds chunk_scan_words(n) words (zeroed here).
-void launch_count_scan(const uint32_t* cnt, int64_t n, uint32_t* off, uint32_t* total, uint32_t* state,
+void launch_count_scan(const uint32_t* cnt, int64_t n, uint32_t* off, uint32_t* total, HostCount host, uint32_t* state,
                        uint32_t* err, hipStream_t st);
 
 // density.hip: rotation and scale of Sigma_cond; the density-control plan

@@ -228,7 +228,7 @@ constexpr int kPsum = 16, kPsumStride = 32;  // words of one sum, a cache line a
 template <class F, class G, bool FLAGS, bool HIST>
 __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap,
                                                   uint32_t* ticket, uint64_t* status, uint32_t* total_out,
-                                                  uint32_t* ghist, uint32_t* psum, uint32_t* err) {
+                                                  uint32_t* ghist, uint32_t* psum, HostCount host, uint32_t* err) {
   __shared__ uint32_t s_blk, s_pre;
   __shared__ uint32_t s_h[HIST ? kMaxPasses : 1][256];
   const int t = threadIdx.x;
@@ -242,7 +242,10 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
   const uint32_t count = load_count(count_ptr, fixed, cap);
   const int64_t start = blk * kChunk;
   if (start >= count) {  // uniform
-    if (blk == 0 && t == 0 && total_out) *total_out = 0u;
+    if (blk == 0 && t == 0 && total_out) {
+      *total_out = 0u;
+      publish(host, 0u);
+    }
     return;
   }
   const int64_t base = start + (int64_t)t * kItems;
@@ -277,7 +280,10 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
       st_store64(my, kSc64Incl | (uint32_t)(excl + total));
     }
     s_pre = excl;
-    if (start + kChunk >= count && total_out) *total_out = excl + total;
+    if (start + kChunk >= count && total_out) {
+      *total_out = excl + total;
+      publish(host, excl + total);
+    }
   }
   __syncthreads();
   pre += s_pre;
@@ -306,11 +312,11 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
 
 template <bool FLAGS, bool HIST, class F, class G>
 void scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap, int64_t bound, uint32_t* ticket,
-           uint64_t* status, uint32_t* total_out, uint32_t* ghist, uint32_t* psum, uint32_t* err, hipStream_t st) {
+           uint64_t* status, uint32_t* total_out, uint32_t* ghist, uint32_t* psum, HostCount host, uint32_t* err, hipStream_t st) {
   int64_t nb = (bound + kChunk - 1) / kChunk;
   if (nb < 1) nb = 1;  // one workgroup writes a zero total
   hipLaunchKernelGGL((k_scan1<F, G, FLAGS, HIST>), dim3((unsigned)nb), dim3(kBlock), 0, st, f, g, count_ptr, fixed, cap,
-                     ticket, status, total_out, ghist, psum, err);
+                     ticket, status, total_out, ghist, psum, host, err);
 }
 
 // Up to four word ranges a preparation kernel zeroes.
@@ -703,12 +709,13 @@ __global__ void __launch_bounds__(kBlock) k_rank(const uint32_t* __restrict__ ke
   }
 #pragma unroll
   for (int r = 0; r < 4; r++) k[r] += j0 < i0 + 64 * r ? 1u : 0u;  // all before i: equal ones count (keys are below 2^31)
-#pragma unroll 8
-  for (int j = 0; j < (int)segment; j++) {
-    const uint32_t q = (uint32_t)__builtin_amdgcn_readlane(kj, j);
+  for (int j = 0; j < (int)segment; j += 8)  // (segments are 16 or 64)
 #pragma unroll
-    for (int r = 0; r < 4; r++) c[r] += q < k[r] ? 1u : 0u;
-  }
+    for (int u = 0; u < 8; u++) {
+      const uint32_t q = (uint32_t)__builtin_amdgcn_readlane(kj, j + u);
+#pragma unroll
+      for (int r = 0; r < 4; r++) c[r] += q < k[r] ? 1u : 0u;
+    }
 #pragma unroll
   for (int r = 0; r < 4; r++)
     if (i0 + 64 * r + lane < n && c[r]) atomicAdd(&place[i0 + 64 * r + lane], c[r]);
@@ -720,7 +727,8 @@ __global__ void __launch_bounds__(kBlock) k_rank(const uint32_t* __restrict__ ke
 __global__ void __launch_bounds__(kBlock) k_rects(ViewTable vt, const Rec* __restrict__ rec,
                                                   const uint32_t* __restrict__ dval,
                                                   const uint32_t* __restrict__ place, uint32_t* __restrict__ dsorted,
-                                                  const uint32_t* __restrict__ psum, uint32_t* __restrict__ counters,
+                                                  const uint32_t* __restrict__ psum, HostCount host,
+                                                  uint32_t* __restrict__ counters,
                                                   uint32_t* __restrict__ rect0, uint32_t* __restrict__ rect1) {
   const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
   if (blockIdx.x == 0 && threadIdx.x < 64) {
@@ -728,6 +736,7 @@ __global__ void __launch_bounds__(kBlock) k_rects(ViewTable vt, const Rec* __res
     if (threadIdx.x == 63) {
       counters[1] = s;
       counters[7] = 0u;
+      publish(host, s);
     }
   }
   if (i >= counters[0]) return;
@@ -1417,6 +1426,7 @@ RadixState depth_state(const SortBuffers& b) {
 // in one 1600x900 view, 50M tests, 220 and 196.
 namespace {
 inline bool test_entries(int64_t E, int64_t patches) { return E * patches <= (1ll << 25); }
+inline bool tests_entries(const SortBuffers& b) { return test_entries(b.E, b.total_patches); }
 // Entries per workgroup of the tests: 1,024 collect more of a patch's entries
 // at once, 256 make enough workgroups of a small call (1.5M tests: the same;
 // 4M: 82 us with 1,024 and 91 with 256).
@@ -1432,6 +1442,8 @@ RadixState pair_state(const SortBuffers& b, int64_t bound, int items) {
                      pair_zero_words(b.total_tiles) - (kGhCopies + 1) * kGhStride);
 }
 }  // namespace
+
+bool sorts_items(const SortBuffers& b) { return !tests_entries(b); }
 
 // One preparation for the whole stage: the depth sort's state, the pair
 // sort's histograms, the tile ranges, the tile order's counts and the
@@ -1472,7 +1484,7 @@ void launch_bin_count(SortBuffers& b, const ViewTable& vt, bool prepped, hipStre
   if (rank_entries(b.E)) {
     place = reinterpret_cast<uint32_t*>(rs.scan_status + 2 * rs.nscan);
     scan1<true, false>(tc, cd, nullptr, E, E, b.E, ticket, rs.scan_status, &b.counters[0], (uint32_t*)nullptr, psum,
-                       &b.counters[3], st);
+                       HostCount{}, &b.counters[3], st);
     const uint32_t segment = rank_segment(b.E);
     if (E)
       hipLaunchKernelGGL(k_rank, dim3((E + kBlock * 4 - 1) / (kBlock * 4), (E + segment - 1) / segment), dim3(kBlock),
@@ -1480,22 +1492,22 @@ void launch_bin_count(SortBuffers& b, const ViewTable& vt, bool prepped, hipStre
     b.dsorted = 1;
   } else {
     scan1<true, true>(tc, cd, nullptr, E, E, b.E, ticket, rs.scan_status, &b.counters[0], rs.ghist, psum,
-                      &b.counters[3], st);
+                      HostCount{}, &b.counters[3], st);
     b.dsorted = radix_sort(b.dkey, b.dval, &b.counters[0], b.E, plan, rs, &b.counters[3], st);
   }
   hipLaunchKernelGGL(k_rects, dim3(std::max(1u, (E + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, vt, b.rec,
                      (const uint32_t*)b.dval[place ? 0 : b.dsorted], (const uint32_t*)place, b.dval[1],
-                     (const uint32_t*)psum, b.counters, b.dkey[0], b.dkey[1]);
+                     (const uint32_t*)psum, b.host_pairs, b.counters, b.dkey[0], b.dkey[1]);
   // item offsets in depth order
-  if (!test_entries(b.E, b.total_patches))
+  if (!tests_entries(b))
     scan1<false, false>(PatchCount{b.dkey[0], b.dkey[1]},
                  StoreOffset{b.poff, b.blk_start, b.nblk_start, (int64_t)kBlock * sort_items(b.pcap)},
                  &b.counters[0], 0u, E, b.E, rs.tickets + kMaxPasses + 1, rs.scan_status + rs.nscan, &b.counters[7],
-                 (uint32_t*)nullptr, (uint32_t*)nullptr, &b.counters[3], st);
+                 (uint32_t*)nullptr, (uint32_t*)nullptr, b.host_items, &b.counters[3], st);
 }
 
 void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t items_hint, bool regrown, hipStream_t st) {
-  const bool direct = test_entries(b.E, b.total_patches);
+  const bool direct = tests_entries(b);
   const int64_t bound = direct ? 0 : items_hint < b.pcap ? items_hint : b.pcap;
   const int items = sort_items(b.pcap);
   const uint32_t chunk = (uint32_t)(kBlock * items), cap = (uint32_t)b.pcap;
@@ -1524,7 +1536,7 @@ void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t items_hint, bo
                        b.order_state, (const uint32_t*)b.tiles, b.E, b.g2d);
     scan1<false, false>(CountVal{b.tile_order}, StoreRange{b.ranges}, nullptr, T, T, T, rs.tickets,
                  reinterpret_cast<uint64_t*>(rs.tickets + kGhStride), (uint32_t*)nullptr, (uint32_t*)nullptr,
-                 (uint32_t*)nullptr, &b.counters[3], st);
+                 (uint32_t*)nullptr, HostCount{}, &b.counters[3], st);
   };
   const unsigned ow = order_wgs(T);
   int cur = 0;
@@ -1596,13 +1608,13 @@ __global__ void __launch_bounds__(kBlock) k_zero_words(uint32_t* __restrict__ p,
 }
 }  // namespace
 
-void launch_count_scan(const uint32_t* cnt, int64_t n, uint32_t* off, uint32_t* total, uint32_t* state,
+void launch_count_scan(const uint32_t* cnt, int64_t n, uint32_t* off, uint32_t* total, HostCount host, uint32_t* state,
                        uint32_t* err, hipStream_t st) {
   const int64_t words = chunk_scan_words(n);
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, state, words);
   const uint32_t N = (uint32_t)n;
   scan1<false, false>(CountVal{cnt}, CountOffset{off}, nullptr, N, N, n, state, reinterpret_cast<uint64_t*>(state + 2), total,
-               (uint32_t*)nullptr, (uint32_t*)nullptr, err, st);
+               (uint32_t*)nullptr, (uint32_t*)nullptr, host, err, st);
 }
 
 int64_t sort_state_words(int64_t bound, bool pairs) {
