@@ -669,18 +669,21 @@ struct CompactDepth {
     }
   }
 };
-// The tile rectangle of a sorted entry: x first | x last << 11 | view << 22,
-// and y first | y last << 11 (a view has at most 2,048 tiles each way); an
-// empty one is in no patch.
+// The tile rectangle of a sorted entry: x first | y first << 16, and x last | y
+// last << 16, with y counted on from one view to the next by 2,048 (a view has
+// at most 2,048 tiles each way, so each half is a non-negative int16 and one
+// packed subtraction compares both); an empty one is in no patch.
 __device__ __forceinline__ uint2 entry_rect(const ViewTable& vt, const Rec* rec, uint32_t e) {
   const uint32_t view = e / (uint32_t)vt.n;
   const ViewDesc& vd = vt.v[view];
   const float4 ra = rec[e].a, rb = rec[e].b;
   int x0, y0, x1, y1;
   tile_rect(ra.x, ra.y, rb.z, rb.w, vt.tile_shift_x, vt.tile_shift_y, vd.ntx, vd.nty, x0, y0, x1, y1);
-  if (x1 <= x0 || y1 <= y0) return make_uint2(2047u, 2047u);  // x last = y last = 0: before the first
-  return make_uint2((uint32_t)(x0 | (x1 - 1) << 11) | view << 22, (uint32_t)(y0 | (y1 - 1) << 11));
+  if (x1 <= x0 || y1 <= y0) return make_uint2(2047u, 0u);  // x last 0: before the first
+  const uint32_t base = view << 27;
+  return make_uint2((uint32_t)(x0 | y0 << 16) + base, (uint32_t)((x1 - 1) | (y1 - 1) << 16) + base);
 }
+static_assert(kMaxViews <= 16, "a rectangle's y halves hold 16 views of 2,048 tile rows");
 
 // A short depth sort by counting: entry i's place is the number of entries j
 // before it in (key, j) order.  A wavefront compares 256 entries with a segment
@@ -757,9 +760,9 @@ struct PatchCount {
   const uint32_t* rect0;
   const uint32_t* rect1;
   __device__ uint32_t operator()(int64_t i) const {
-    const uint32_t x = rect0[i], y = rect1[i];
-    const int w = (int)((x >> 14) & 255u) - (int)((x >> 3) & 255u) + 1;
-    const int h = (int)((y >> 14) & 255u) - (int)((y >> 3) & 255u) + 1;
+    const uint32_t r0 = rect0[i], r1 = rect1[i];
+    const int w = (int)((r1 >> 3) & 255u) - (int)((r0 >> 3) & 255u) + 1;
+    const int h = (int)((r1 >> 19) & 255u) - (int)((r0 >> 19) & 255u) + 1;
     return w > 0 && h > 0 ? (uint32_t)(w * h) : 0u;
   }
 };
@@ -814,7 +817,7 @@ __global__ void __launch_bounds__(kBlock) k_emit(ViewTable vt, const uint32_t* _
                                                  uint32_t chunk) {
   __shared__ uint32_t s_o[kBlock + 1];  // item offset of each entry of the step; [kBlock]: the next step's
   __shared__ uint32_t s_e[kBlock];      // entry id
-  __shared__ uint32_t s_x[kBlock], s_y[kBlock];  // its rectangle
+  __shared__ uint32_t s_r0[kBlock], s_r1[kBlock];  // its rectangle
   __shared__ uint32_t s_h[kMaxPasses][256];
   const int t = threadIdx.x;
   // blk_start holds an entry for every workgroup of the grid: read with the
@@ -841,8 +844,8 @@ __global__ void __launch_bounds__(kBlock) k_emit(ViewTable vt, const uint32_t* _
       // search below: its rectangle is not read
       if (o < p1) {
         s_e[t] = dval[i];
-        s_x[t] = rect0[i];
-        s_y[t] = rect1[i];
+        s_r0[t] = rect0[i];
+        s_r1[t] = rect1[i];
       }
     } else {
       s_o[t] = S;  // past the last entry: never chosen by the search below
@@ -857,13 +860,13 @@ __global__ void __launch_bounds__(kBlock) k_emit(ViewTable vt, const uint32_t* _
       for (int step = kBlock / 2; step > 0; step >>= 1)
         if (s_o[j + step] <= q) j += step;
       const uint32_t local = q - s_o[j];
-      const uint32_t rx = s_x[j], ry = s_y[j];
-      const uint32_t px0 = (rx >> 3) & 255u, px1 = (rx >> 14) & 255u, py0 = (ry >> 3) & 255u, py1 = (ry >> 14) & 255u;
+      const uint32_t r0 = s_r0[j], r1 = s_r1[j];
+      const uint32_t px0 = (r0 >> 3) & 255u, px1 = (r1 >> 3) & 255u, py0 = (r0 >> 19) & 255u, py1 = (r1 >> 19) & 255u;
       const uint32_t w = px1 - px0 + 1;
       const uint32_t ty = local / w, px = px0 + (local - ty * w), py = py0 + ty;
-      const uint32_t tiles = (px == px0 ? rx & 7u : 0u) | (px == px1 ? (rx >> 11) & 7u : 7u) << 3 |
-                             (py == py0 ? ry & 7u : 0u) << 6 | (py == py1 ? (ry >> 11) & 7u : 7u) << 9;
-      const ViewDesc& vd = vt.v[rx >> 22];
+      const uint32_t tiles = (px == px0 ? r0 & 7u : 0u) | (px == px1 ? r1 & 7u : 7u) << 3 |
+                             (py == py0 ? (r0 >> 16) & 7u : 0u) << 6 | (py == py1 ? (r1 >> 16) & 7u : 7u) << 9;
+      const ViewDesc& vd = vt.v[r0 >> 27];
       const uint32_t key = tiles << 20 | (vd.patch_base + py * ((vd.ntx + 7) >> 3) + px);
       pkey[q] = key;
       pval[q] = s_e[j];
@@ -1008,6 +1011,10 @@ __device__ __forceinline__ void put_lane(uint32_t& lo, uint32_t& hi, uint64_t m,
 // Has a loaded value waited for here: where it is next used, the wait would
 // also be for the stores in between (one counter holds both).
 __device__ __forceinline__ void arrived(uint32_t& v) { asm volatile("" : "+v"(v)); }
+
+typedef short Short2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ Short2 as_short2(uint32_t v) { return __builtin_bit_cast(Short2, v); }
+__device__ __forceinline__ uint32_t as_uint(Short2 v) { return __builtin_bit_cast(uint32_t, v); }
 
 // the columns and rows x0 .. x1, y0 .. y1 of a patch as 8 + 8 bits
 __device__ __forceinline__ uint32_t patch_bits(uint32_t x0, uint32_t x1, uint32_t y0, uint32_t y1) {
@@ -1257,13 +1264,14 @@ __global__ void __launch_bounds__(kBlock) k_entry_lists(ViewTable vt, const uint
   const ViewDesc& vd = vt.v[view];
   const int npx = (vd.ntx + 7) >> 3, local = (int)patch - vd.patch_base, py = local / npx, px = local - py * npx;
   uint32_t* row = table + ((uint64_t)patch * nchunk + c) * 64;
-  // the rectangles, in tiles from the patch's first, and which of them touch it
+  const Short2 patch_first = {(short)(8 * px), (short)(8 * py + 2048 * (int)view)};
+  const Short2 patch_last = {(short)(8 * px + 7), (short)(8 * py + 7 + 2048 * (int)view)};
   const uint32_t i0 = c * kEntries + wv * (64 * STEPS) + lane;
   uint32_t a[STEPS], b[STEPS], e[STEPS];
 #pragma unroll
   for (int s = 0; s < STEPS; s++) {
     const uint32_t i = i0 + 64 * s;
-    a[s] = i < nb ? rect0[i] : ~0u;  // (no such view)
+    a[s] = i < nb ? rect0[i] : 0x7FFF7FFFu;  // (starts behind every patch)
     b[s] = i < nb ? rect1[i] : 0u;
     e[s] = WRITE && i < nb ? dval[i] : 0u;
   }
@@ -1277,10 +1285,14 @@ __global__ void __launch_bounds__(kBlock) k_entry_lists(ViewTable vt, const uint
   uint32_t mine = 0;
 #pragma unroll
   for (int s = 0; s < STEPS; s++) {
-    const int x0 = (int)(a[s] & 2047u) - 8 * px, x1 = (int)((a[s] >> 11) & 2047u) - 8 * px;
-    const int y0 = (int)(b[s] & 2047u) - 8 * py, y1 = (int)((b[s] >> 11) & 2047u) - 8 * py;
-    const bool hit = a[s] >> 22 == view && x0 < 8 && x1 >= 0 && y0 < 8 && y1 >= 0;
-    a[s] = hit ? patch_bits(max(x0, 0), min(x1, 7), max(y0, 0), min(y1, 7)) : 0u;
+    // to the rectangle's first tile from the patch's last, and to the patch's
+    // first from its last; the entry touches the patch if no half is negative
+    const Short2 d0 = patch_last - as_short2(a[s]), d1 = as_short2(b[s]) - patch_first;
+    const bool hit = ((as_uint(d0) | as_uint(d1)) & 0x80008000u) == 0;
+    const uint32_t f = as_uint(__builtin_elementwise_min(d0, Short2{7, 7}));
+    const uint32_t l = as_uint(__builtin_elementwise_min(d1, Short2{7, 7}));
+    const uint32_t xb = (2u << (l & 7u)) - (128u >> (f & 7u)), yb = (2u << ((l >> 16) & 7u)) - (128u >> ((f >> 16) & 7u));
+    a[s] = hit ? xb | yb << 8 : 0u;
     m[s] = __ballot(hit);
     mine += (uint32_t)__popcll(m[s]);
   }
