@@ -36,10 +36,11 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x) {
   return x;
 }
 
-// Exclusive scan of one value per thread over the workgroup; returns the
-// exclusive prefix and the workgroup total.
+// Exclusive scan of one value per thread over the workgroup of WAVES wavefronts;
+// returns the exclusive prefix and the workgroup total.
+template <int WAVES = kWaves>
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t& total) {
-  __shared__ uint32_t s_w[kWaves];
+  __shared__ uint32_t s_w[WAVES];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   uint32_t inc = wave_scan_incl(x);
   if (lane == 63) s_w[wv] = inc;
@@ -47,7 +48,7 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t& total)
   uint32_t before = 0;
   total = 0;
 #pragma unroll
-  for (int w = 0; w < kWaves; w++) {
+  for (int w = 0; w < WAVES; w++) {
     const uint32_t s = s_w[w];
     before += (w < wv) ? s : 0u;
     total += s;
@@ -221,26 +222,28 @@ __device__ uint32_t look_back(const W* status, int64_t stride, int64_t blk, uint
 constexpr int kPsum = 16, kPsumStride = 32;  // words of one sum, a cache line apart
 
 // Single-pass exclusive scan of f(i) over i < count, handing (i, prefix,
-// value) to g.  Workgroups take 2048 items each in ticket order and chain
-// their prefixes through look-back words; the workgroup holding the last item
+// value) to g.  Workgroups take 2048 items each in ticket order (8192 from
+// kLargeSort items on, where taking the tickets, 17 ns apart, bounded it: 8M
+// entries 101 -> 61 us) and chain their prefixes through look-back words; the workgroup holding the last item
 // writes the total.  With HIST, g.key(i) of every item with a non-zero value
 // also enters the digit histograms of a 4-pass, 8-bit radix sort.
-template <class F, class G, bool FLAGS, bool HIST>
-__global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap,
+template <class F, class G, bool FLAGS, bool HIST, int THREADS>
+__global__ void __launch_bounds__(THREADS) k_scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap,
                                                   uint32_t* ticket, uint64_t* status, uint32_t* total_out,
                                                   uint32_t* ghist, uint32_t* psum, HostCount host, uint32_t* err) {
   __shared__ uint32_t s_blk, s_pre;
   __shared__ uint32_t s_h[HIST ? kMaxPasses : 1][256];
+  constexpr int kChunkT = THREADS * kItems;
   const int t = threadIdx.x;
   if (t == 0) s_blk = atomicAdd(ticket, 1u);
-  if (HIST) {
+  if (HIST && t < 256) {
 #pragma unroll
     for (int p = 0; p < kMaxPasses; p++) s_h[p][t] = 0;
   }
   __syncthreads();
   const int64_t blk = s_blk;
   const uint32_t count = load_count(count_ptr, fixed, cap);
-  const int64_t start = blk * kChunk;
+  const int64_t start = blk * kChunkT;
   if (start >= count) {  // uniform
     if (blk == 0 && t == 0 && total_out) {
       *total_out = 0u;
@@ -256,31 +259,56 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
     v[k] = (base + k < count) ? f(base + k) : 0u;
     sum += v[k];
   }
+  uint32_t key[FLAGS ? kItems : 1];
   if constexpr (FLAGS) {
     uint32_t all;
-    block_scan_excl(sum, all);
+    block_scan_excl<THREADS / 64>(sum, all);
     if (t == 0 && all) atomicAdd(&psum[blk % kPsum * kPsumStride], all);
     sum = 0;
 #pragma unroll
     for (int k = 0; k < kItems; k++) {
+      key[k] = v[k] ? g.key(base + k) : 0u;
       v[k] = v[k] ? 1u : 0u;
       sum += v[k];
     }
   }
   uint32_t total;
-  uint32_t pre = block_scan_excl(sum, total);
+  uint32_t pre = block_scan_excl<THREADS / 64>(sum, total);
+  uint64_t* my = status + blk;
+  if (t == 0) st_store64(my, (blk == 0 ? kSc64Incl : kSc64Agg) | total);
+  if constexpr (HIST) {
+    // (before the wait on earlier workgroups.)  The lanes whose upper digits
+    // equal the first's add as one: depths share them, and same-address
+    // shared-memory atomics serialise
+#pragma unroll
+    for (int k = 0; k < kItems; k++) {
+      if (v[k]) {
+        const bool leader = __lane_id() == (unsigned)(__ffsll((unsigned long long)__ballot(1)) - 1);
+#pragma unroll
+        for (int p = 0; p < kMaxPasses; p++) {
+          const uint32_t d = (key[k] >> (8 * p)) & 255u;
+          if (p < 2) {
+            atomicAdd(&s_h[p][d], 1u);
+          } else {
+            const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
+            const uint64_t same = __ballot(d == d0);
+            if (d != d0)
+              atomicAdd(&s_h[p][d], 1u);
+            else if (leader)
+              atomicAdd(&s_h[p][d0], (uint32_t)__popcll(same));
+          }
+        }
+      }
+    }
+  }
   if (t == 0) {
-    uint64_t* my = status + blk;
     uint32_t excl = 0;
-    if (blk == 0) {
-      st_store64(my, kSc64Incl | total);
-    } else {
-      st_store64(my, kSc64Agg | total);
+    if (blk > 0) {
       excl = look_back(status, 1, blk, err);
       st_store64(my, kSc64Incl | (uint32_t)(excl + total));
     }
     s_pre = excl;
-    if (start + kChunk >= count && total_out) {
+    if (start + kChunkT >= count && total_out) {
       *total_out = excl + total;
       publish(host, excl + total);
     }
@@ -289,34 +317,34 @@ __global__ void __launch_bounds__(kBlock) k_scan1(F f, G g, const uint32_t* coun
   pre += s_pre;
 #pragma unroll
   for (int k = 0; k < kItems; k++) {
-    if (base + k < count) {
-      g(base + k, pre, v[k]);
-      if constexpr (HIST) {
-        if (v[k]) {
-          const uint32_t key = g.key(base + k);
-#pragma unroll
-          for (int p = 0; p < kMaxPasses; p++) atomicAdd(&s_h[p][(key >> (8 * p)) & 255u], 1u);
-        }
-      }
+    if constexpr (FLAGS) {
+      if (v[k]) g.put(base + k, pre, key[k]);
+    } else {
+      if (base + k < count) g(base + k, pre, v[k]);
     }
     pre += v[k];
   }
-  if (HIST) {
-    __syncthreads();
+  if constexpr (HIST) {  // (every wavefront's adds are in: the barrier above)
     uint32_t* gh = ghist_copy(ghist, blk);
 #pragma unroll
     for (int p = 0; p < kMaxPasses; p++)
-      if (s_h[p][t]) atomicAdd(&gh[p * 256 + t], s_h[p][t]);
+      if (t < 256 && s_h[p][t]) atomicAdd(&gh[p * 256 + t], s_h[p][t]);
   }
 }
 
 template <bool FLAGS, bool HIST, class F, class G>
 void scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap, int64_t bound, uint32_t* ticket,
            uint64_t* status, uint32_t* total_out, uint32_t* ghist, uint32_t* psum, HostCount host, uint32_t* err, hipStream_t st) {
-  int64_t nb = (bound + kChunk - 1) / kChunk;
-  if (nb < 1) nb = 1;  // one workgroup writes a zero total
-  hipLaunchKernelGGL((k_scan1<F, G, FLAGS, HIST>), dim3((unsigned)nb), dim3(kBlock), 0, st, f, g, count_ptr, fixed, cap,
-                     ticket, status, total_out, ghist, psum, host, err);
+  auto launch = [&](auto kernel, int threads) {
+    const int64_t chunk = (int64_t)threads * kItems;
+    const int64_t nb = std::max<int64_t>((bound + chunk - 1) / chunk, 1);  // one workgroup writes a zero total
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(threads), 0, st, f, g, count_ptr, fixed, cap, ticket, status,
+                       total_out, ghist, psum, host, err);
+  };
+  if (bound >= kLargeSort)
+    launch(k_scan1<F, G, FLAGS, HIST, 1024>, 1024);
+  else
+    launch(k_scan1<F, G, FLAGS, HIST, kBlock>, kBlock);
 }
 
 // Up to four word ranges a preparation kernel zeroes.
@@ -662,11 +690,9 @@ struct CompactDepth {
   uint32_t* dval;
   // depths of binned entries exceed z_near > 0, so their bit patterns order as the values
   __device__ uint32_t key(int64_t i) const { return __float_as_uint(depth[i]); }
-  __device__ void operator()(int64_t i, uint32_t pre, uint32_t v) const {
-    if (v) {
-      dkey[pre] = key(i);
-      dval[pre] = (uint32_t)i;
-    }
+  __device__ void put(int64_t i, uint32_t pre, uint32_t key) const {
+    dkey[pre] = key;
+    dval[pre] = (uint32_t)i;
   }
 };
 // The tile rectangle of a sorted entry: x first | y first << 16, and x last | y
