@@ -721,12 +721,14 @@ __global__ void __launch_bounds__(kBlock) k_rank(const uint32_t* __restrict__ ke
   const uint32_t n = counters[0];
   const uint32_t i0 = (blockIdx.x * kWaves + wv) * 256, j0 = blockIdx.y * segment;
   if (i0 >= n || j0 >= n) return;
-  const uint32_t kj = j0 + lane < n ? key[j0 + lane] : ~0u;  // (nothing is after these)
+  // keys below ~0 (a caller's depth may be any bit pattern), so that one more is
+  // still a key; ~0 past the last entry, before which everything is
+  const uint32_t kj = j0 + lane < n ? min(key[j0 + lane], ~1u) : ~0u;
   uint32_t k[4], c[4] = {0, 0, 0, 0};
 #pragma unroll
   for (int r = 0; r < 4; r++) {
     const uint32_t i = i0 + 64 * r + lane;
-    k[r] = i < n ? key[i] : 0u;
+    k[r] = i < n ? min(key[i], ~1u) : 0u;
   }
   if (j0 >= i0 && j0 < i0 + 256) {  // the segment is in the wavefront's own 256: equal keys before i count
     const int own = (int)(j0 - i0) >> 6, off = (int)(j0 - i0) & 63;
@@ -737,7 +739,7 @@ __global__ void __launch_bounds__(kBlock) k_rank(const uint32_t* __restrict__ ke
     for (int r = 0; r < 4; r++) c[r] = r == own ? ties : 0u;
   }
 #pragma unroll
-  for (int r = 0; r < 4; r++) k[r] += j0 < i0 + 64 * r ? 1u : 0u;  // all before i: equal ones count (keys are below 2^31)
+  for (int r = 0; r < 4; r++) k[r] += j0 < i0 + 64 * r ? 1u : 0u;  // all before i: equal ones count
   for (int j = 0; j < (int)segment; j += 8)  // (segments are 16 or 64)
 #pragma unroll
     for (int u = 0; u < 8; u++) {

@@ -46,3 +46,19 @@ def test_lists_bit_exact(sizes, n, ext, tile):
         with pytest.raises(SixDGSError) as e:
             small.ctx.check()
         assert e.value.status == _lib.ERR_CAPACITY
+
+
+def test_depths_of_any_bit_pattern_are_ordered_by_counting():
+    """The caller's depths may be NaN with every bit set: these entries come last
+    in every tile, in entry order, and each stands where it belongs once."""
+    from paper_2410_04974_amd import _lib
+    cams, n = [synth.default_camera(200, 150)], 3000
+    u, v, ex, ey, depth, alive = _random_records(n, cams, seed=3, ext=20.0)
+    odd = np.arange(n) % 3 == 0
+    depth[odd] = 1e30  # where the oracle puts them
+    ref = oracle.bin_records(u, v, ex, ey, depth, alive.astype(bool), n, cams, 16, 16)
+    depth.view(np.uint32)[odd] = 0xFFFFFFFF
+    r = G.renderer()
+    r.ctx.bin(n, cams, *(torch.from_numpy(a).to(G.DEV) for a in (u, v, ex, ey, depth, alive)))
+    r.ctx.check()
+    assert np.array_equal(r.ctx.export(_lib.EXPORT_VALUES), ref["values"].astype(np.int32))
