@@ -911,13 +911,15 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
 }  // namespace
 
 namespace {
+constexpr int kFoursTiles = 3072;  // from this many tiles on the forward goes by pairs
+
 template <int TW>
 void launch_fwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges, const uint32_t* pval,
                 const BlendState& bs, bool save, hipStream_t st) {
-  auto k = !save                       ? k_blend_fwd<TW, false, false, 2, 7>
-           : bs.counts                 ? k_blend_fwd<TW, true, true, 4, 4>
-           : few_tiles(vt.total_tiles) ? k_blend_fwd<TW, true, false, 4, 4>
-                                       : k_blend_fwd<TW, true, false, 2, 6>;
+  auto k = !save                          ? k_blend_fwd<TW, false, false, 2, 7>
+           : bs.counts                    ? k_blend_fwd<TW, true, true, 4, 4>
+           : vt.total_tiles < kFoursTiles ? k_blend_fwd<TW, true, false, 4, 4>
+                                          : k_blend_fwd<TW, true, false, 2, 6>;
   hipLaunchKernelGGL(k, dim3(vt.total_tiles), dim3(kBlock), 0, st, vt, s, rec, ranges, pval, bs);
 }
 }  // namespace

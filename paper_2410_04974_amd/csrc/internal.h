@@ -237,9 +237,8 @@ void launch_import_records(const float* u, const float* v, const float* ex, cons
                            const int32_t* alive, const ViewTable& vt, Rec* rec, uint32_t* tiles, hipStream_t st);
 
 // blend.hip
-// Below this many tiles in a call the compositing is bound by its longest
-// walks rather than by its work: the forward then takes its form for those, and
-// the backward's automatic chunk and batch depth are the short ones.
+// Below this many tiles in a call the backward is bound by its longest walks
+// rather than by its work: its automatic chunk and batch depth are the short ones.
 constexpr int64_t kAutoTiles = 16384;
 inline bool few_tiles(int64_t total_tiles) { return total_tiles < kAutoTiles; }
 // The backward splits each tile's list into work items of `chunk` list
