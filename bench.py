@@ -231,7 +231,7 @@ def alg_bytes(n, nb, P, px, tiles):
     in the view, P (tile, Gaussian) pairs, px pixels)."""
     return {
         "preprocess": 304 * n + 4 * n + 52 * nb,            # params; tile count; record + depth
-        "binning": 64 * nb + 24 * P + 4 * P + 8 * tiles,    # depth sort; pair build + tile sort; ranges
+        "binning": 64 * nb + 4 * P + 8 * tiles,             # depth sort; the tiles' lists; ranges
         "blend_fwd": 40 * P + 20 * px,                      # record per pair; colour, T, last per pixel
         "l1": 12 * 3 * px,                                  # image, target, gradient
         "blend_bwd": 40 * P + 32 * px + 36 * nb,            # as the forward + dL/dI; screen-space gradients
