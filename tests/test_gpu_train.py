@@ -179,6 +179,43 @@ def test_fused_step_count_on_the_device_matches_the_host_count():
     assert int(cnt.item()) == 7
 
 
+@pytest.mark.parametrize("views", [1, 2])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000, 32768, 32769])
+def test_fused_step_at_the_edges_of_its_forms(n, views):
+    """The fused backward + Adam where its workgroups end and where its form
+    changes (32,768 Gaussians), against the gradient written out by the same
+    chain rule and the Adam formulas in float64.  The two backward passes of
+    one forward differ only in the order of float atomics, so the moments
+    after a first step agree to the gradients' rounding; the parameters are
+    compared where the gradient is well above it (an update is lr * sign(g) at
+    first)."""
+    from paper_2410_04974_amd import Renderer
+    w, pn = G.scene("c2", n)
+    cams = [synth.default_camera(160, 128), synth.default_camera(97, 61)][:views]
+    p = torch.from_numpy(pn).to(G.DEV)
+    r = Renderer()
+    r.forward(p, cams)
+    dl = [torch.from_numpy(d).to(G.DEV) for d in synth.upstream_gradient(cams)]
+    grad, dens0 = torch.zeros_like(p), torch.zeros((2, n), device=G.DEV)
+    r.ctx.backward(p, dl, grad, densify=dens0)
+    m, v, dens1 = torch.zeros_like(p), torch.zeros_like(p), torch.zeros((2, n), device=G.DEV)
+    cnt = torch.zeros((1,), device=G.DEV, dtype=torch.int32)
+    lr = [0.01, 0.02, 0.03, 0.04, 0.05, 0.06]
+    r.ctx.backward_adam(p, dl, m, v, lr, step_counter=cnt, densify=dens1)
+    torch.cuda.synchronize()
+    assert int(cnt.item()) == 1
+    g = grad.cpu().numpy().astype(np.float64)
+    scale = max(1e-30, np.abs(g).max())
+    assert np.abs(m.cpu().numpy() / 0.1 - g).max() <= 1e-4 * scale
+    assert np.abs(np.sqrt(v.cpu().numpy() / 1e-3) - np.abs(g)).max() <= 1e-4 * scale
+    assert np.allclose(dens0.cpu().numpy(), dens1.cpu().numpy(), rtol=1e-3, atol=1e-4 * max(1e-30, float(dens0.max())))
+    rows = np.array([0] * 3 + [1] * 3 + [2] * 21 + [3] * 3 + [4] * 45 + [5])
+    step = pn.astype(np.float64) - p.cpu().numpy()
+    sure = np.abs(g) > 1e-3 * scale
+    want = np.broadcast_to(np.array(lr)[rows][:, None], g.shape) * np.sign(g)
+    assert np.allclose(step[sure], want[sure], rtol=1e-3, atol=1e-6 * max(1.0, np.abs(pn).max()))
+
+
 def test_densify_statistics_match_oracle():
     w, pn = G.scene("c1", 15000)
     cams = [synth.default_camera(160, 128), synth.look_at_camera((0.0, -4.0, 1.0), 96, 80)]
