@@ -76,7 +76,7 @@ struct __align__(16) Rec {
 constexpr int kG2D = 9;
 
 // Tile rectangle [x0, x1) x [y0, y1) of an extent box, the one definition used
-// by both the projection (to count tiles) and the pair emission (to list them).
+// by the projection (to count tiles) and by the integer stage (to list them).
 __device__ __forceinline__ void tile_rect(float u, float v, float ex, float ey, int shift_x, int shift_y, int ntx,
                                           int nty, int& x0, int& y0, int& x1, int& y1) {
   const float ix = 1.0f / (float)(1 << shift_x);
