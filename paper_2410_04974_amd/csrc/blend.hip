@@ -609,13 +609,27 @@ struct BwdWave {
   uint32_t qmin;        // list positions before here no pixel compares
 };
 
+// The gradients are moments of w = dL/d(exponent).  Far along a long thin
+// Gaussian dx and dy are large and, in the gradients of its mean and covariance,
+// nearly cancel.  So the walk takes the moments of (x, dy) with x = dx + r dy,
+// the pixel's distance along its line from the Gaussian's axis, and they become
+// those of (dx, dy) once per staged Gaussian (needles of 40 to 300 pixels: mean
+// off by 3e-8 of its terms' sum, covariance by 2e-6 to 5e-6 in the root mean;
+// moments of (dx, dy) throughout: 1e-7, and 2e-6 to 9e-6).  r = 0 where cB/2 / cA
+// is not a number that serves.
+__device__ __forceinline__ float axis_slope(float cA, float cB) {
+  const float r = 0.5f * cB * rcp_fast(cA);
+  return fabsf(r) < 1e12f ? r : 0.f;
+}
+
 // A group's Gaussian in this lane, and its sums over the pixels of the row.
 struct BwdGauss {
   float cA;
   float dx[8];                // pixel columns
-  float bdy[2], cdy[2];       // the exponent's terms of the row's two pixel lines (4 apart)
+  float r, dy[2];             // axis_slope; the row's two pixel lines (4 apart)
+  float bdy[2], cdy[2];       // the exponent's terms of the lines
   uint32_t pos;               // list position
-  float s0[2], s1[2], s2[2];  // per pixel line: sums of w, w dx, w dx^2 (w = dL/d(exponent))
+  float s0[2], s1[2], s2[2];  // per pixel line: sums of w, w x, w x^2 (w = dL/d(exponent))
   float col[3];               // colour gradient
 };
 
@@ -663,16 +677,20 @@ __device__ __forceinline__ void bwd_steps(BwdWave& W, BwdGauss& G, float col) {
   colour_terms<K>(G.col, W.dC, wgt);
   // alpha dL/dalpha = T alpha dL/dC . c - alpha / (1 - alpha) dL/dC . (colour behind)
   behind_terms<K>(W.D, q, f, W.one);
+  if constexpr (FORM == kExact) {
 #pragma unroll
-  for (int j = 0; j < 4; j++) {
-    const float dx = G.dx[(4 * K + j) & 7];
-    float w = q[j];
-    if constexpr (FORM == kExact) w = e[j] <= kAlphaMax ? w : 0.f;  // zero derivative above the clamp
-    const float w1 = w * dx;
-    G.s0[h] += w;
-    G.s1[h] += w1;
-    G.s2[h] = __fmaf_rn(w1, dx, G.s2[h]);
+    for (int j = 0; j < 4; j++) q[j] = e[j] <= kAlphaMax ? q[j] : 0.f;  // zero derivative above the clamp
   }
+  // the four pixels' moments about the second's column, then about the axis
+  const float a02 = q[0] + q[2];
+  const float m0 = a02 + (q[1] + q[3]);
+  const float m1 = __fmaf_rn(2.f, q[3], q[2] - q[0]);
+  const float m2 = __fmaf_rn(4.f, q[3], a02);
+  const float x1 = __fmaf_rn(G.r, G.dy[h], G.dx[(4 * K + 1) & 7]);
+  const float c1 = __fmaf_rn(x1, m0, m1);
+  G.s0[h] += m0;
+  G.s1[h] += c1;
+  G.s2[h] += __fmaf_rn(x1, m1 + c1, m2);
 }
 
 // pos0: the group's first list position; a 4 x 4 quad of pixels that all ended
@@ -805,7 +823,6 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
     W.qlast[k] = __builtin_amdgcn_readfirstlane(wave_max(mine ? last : 0u));
   }
   const uint32_t cend = min(cstart + chunk, maxlast);
-  const float kq = -0.5f * kLog2e;
 
   for (uint32_t bend = rg.x + cend; bend > rg.x + cstart;) {
     const uint32_t b0 = (bend - (rg.x + cstart) > (uint32_t)batch) ? bend - batch : rg.x + cstart;
@@ -827,12 +844,13 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
       G.cA = A.z;
 #pragma unroll
       for (int k = 0; k < 8; k++) G.dx[k] = fx[k] - A.x;
-      float dy[2];
+      G.r = axis_slope(A.z, A.w);
 #pragma unroll
       for (int h = 0; h < 2; h++) {
-        dy[h] = (by0 + 4.f * (float)h) - A.y;
-        G.bdy[h] = __fmul_rn(A.w, dy[h]);
-        G.cdy[h] = __fmaf_rn(__fmul_rn(B.x, dy[h]), dy[h], B.y);
+        const float dy = (by0 + 4.f * (float)h) - A.y;
+        G.dy[h] = dy;
+        G.bdy[h] = __fmul_rn(A.w, dy);
+        G.cdy[h] = __fmaf_rn(__fmul_rn(B.x, dy), dy, B.y);
         G.s0[h] = G.s1[h] = G.s2[h] = 0.f;
       }
       G.col[0] = G.col[1] = G.col[2] = 0.f;
@@ -843,13 +861,13 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
         bwd_group<kStops>(W, G, col, pos0);
       else
         bwd_group<kFree>(W, G, col, pos0);
-      // the moments of w about the Gaussian's centre and the colour gradient,
-      // summed over the four rows (halving exchanges) and added in LDS
+      // the moments of w in (x, dy) and the colour gradient, summed over the
+      // four rows (halving exchanges) and added in LDS
       const float v[kG2D] = {G.s1[0] + G.s1[1],
-                             dy[0] * G.s0[0] + dy[1] * G.s0[1],
+                             G.dy[0] * G.s0[0] + G.dy[1] * G.s0[1],
                              G.s2[0] + G.s2[1],
-                             dy[0] * G.s1[0] + dy[1] * G.s1[1],
-                             dy[0] * dy[0] * G.s0[0] + dy[1] * dy[1] * G.s0[1],
+                             G.dy[0] * G.s1[0] + G.dy[1] * G.s1[1],
+                             G.dy[0] * G.dy[0] * G.s0[0] + G.dy[1] * G.dy[1] * G.s0[1],
                              G.s0[0] + G.s0[1],
                              G.col[0],
                              G.col[1],
@@ -883,15 +901,18 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
 #pragma unroll
       for (int k = 0; k < kG2D; k++) v[k] = s_g[t * kG2D + k];
       // exponent p2 = log2(alpha) = cA dx^2 + cB dx dy + cC dy^2 + log2(alpha_cond), with
-      // dx = x - u: dp2/du = -(2 cA dx + cB dy), dp2/dv = -(cB dx + 2 cC dy); and
+      // dx = x - r dy: dp2/dmean = -2 (cA dx + hB dy, hB dx + cC dy) for hB = cB / 2, and
       // dp2/dcA = dx^2 etc., cA = kq Qxx, cB = 2 kq Qxy, cC = kq Qyy
       const Staged& sr = L.rec[t];
-      const float m0 = v[0] * kLn2, m1 = v[1] * kLn2;  // moments of dL/dp2 = dL/dp ln 2
-      s_g[t * kG2D + 0] = -(2.f * sr.a.z * m0 + sr.a.w * m1);
-      s_g[t * kG2D + 1] = -(sr.a.w * m0 + 2.f * sr.b.x * m1);
-      s_g[t * kG2D + 2] = v[2] * (kLn2 * kq);
-      s_g[t * kG2D + 3] = v[3] * (kLn2 * kq);
-      s_g[t * kG2D + 4] = v[4] * (kLn2 * kq);
+      const float cA = sr.a.z, hB = 0.5f * sr.a.w, r = axis_slope(sr.a.z, sr.a.w);
+      const float e = __fmaf_rn(-cA, r, hB), g = __fmaf_rn(-hB, r, sr.b.x);
+      constexpr float kMean = -2.f * kLn2, kConic = -0.5f * kLog2e * kLn2;  // (dL/dp2 = ln 2 w)
+      s_g[t * kG2D + 0] = kMean * (cA * v[0] + e * v[1]);
+      s_g[t * kG2D + 1] = kMean * (hB * v[0] + g * v[1]);
+      const float xy = __fmaf_rn(-r, v[4], v[3]);  // the sum of w dx dy
+      s_g[t * kG2D + 2] = kConic * __fmaf_rn(-r, v[3] + xy, v[2]);
+      s_g[t * kG2D + 3] = kConic * xy;
+      s_g[t * kG2D + 4] = kConic * v[4];
       s_g[t * kG2D + 5] = v[5] * fabsf(sr.b.z);  // d alpha / d alpha_cond = alpha / alpha_cond
       s_ent[t] = __float_as_uint(sr.b.w);
     }

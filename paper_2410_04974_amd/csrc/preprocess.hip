@@ -432,13 +432,14 @@ __device__ __forceinline__ void bwd_gaussian(const float* params, int64_t n, int
     const float z = w.p[2], fx = vd.fx, fy = vd.fy;
     dens_norm += M::sqrt((gu * 0.5f * vd.W) * (gu * 0.5f * vd.W) + (gv * 0.5f * vd.H) * (gv * 0.5f * vd.H));
     dens_cnt += 1.f;
-    // conic -> 2D covariance: G_S = -Q G_Q Q
-    const float Q00 = w.Q[0], Q01 = w.Q[1], Q11 = w.Q[2];
-    const float QG00 = Q00 * gqxx + Q01 * gqxy, QG01 = Q00 * gqxy + Q01 * gqyy;
-    const float QG10 = Q01 * gqxx + Q11 * gqxy, QG11 = Q01 * gqxy + Q11 * gqyy;
-    const float GS00 = -(QG00 * Q00 + QG01 * Q01);
-    const float GS01 = -(QG00 * Q01 + QG01 * Q11);
-    const float GS11 = -(QG10 * Q01 + QG11 * Q11);
+    // conic -> 2D covariance: G_S = -Q G_Q Q, whose products nearly cancel for a
+    // long thin Gaussian: in 64 bits
+    const double Q00 = w.Q[0], Q01 = w.Q[1], Q11 = w.Q[2];
+    const double QG00 = Q00 * gqxx + Q01 * gqxy, QG01 = Q00 * gqxy + Q01 * gqyy;
+    const double QG10 = Q01 * gqxx + Q11 * gqxy, QG11 = Q01 * gqxy + Q11 * gqyy;
+    const float GS00 = (float)-(QG00 * Q00 + QG01 * Q01);
+    const float GS01 = (float)-(QG00 * Q01 + QG01 * Q11);
+    const float GS11 = (float)-(QG10 * Q01 + QG11 * Q11);
     const float GS[2][2] = {{GS00, GS01}, {GS01, GS11}};
     // Sigma_2D = T Sigma_c T^T + dil I:  dSigma_c = T^T G_S T,  dT = 2 G_S T Sigma_c
     float GT[2][3];
