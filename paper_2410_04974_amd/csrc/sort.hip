@@ -12,6 +12,7 @@
 // sized by a host-side upper bound, so the stage needs no host round trip
 // (and can be captured) when the pair capacity is fixed.
 #include "internal.h"
+#include "pairs.h"
 
 namespace sixdgs {
 namespace {
@@ -221,7 +222,23 @@ __device__ uint32_t look_back(const W* status, int64_t stride, int64_t blk, uint
   return excl;
 }
 
-constexpr int kPsum = 16, kPsumStride = 32;  // words of one sum, a cache line apart
+constexpr int kPsum = 16, kPsumStride = 16;  // 64-bit words of one sum, a cache line apart
+
+// A workgroup's total of x (each wavefront's saturated), added to *sum.
+template <int WAVES>
+__device__ __forceinline__ void block_add(uint32_t x, uint64_t* sum) {
+  __shared__ uint32_t s_w[WAVES];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x = __builtin_elementwise_add_sat(x, (uint32_t)__shfl_xor((int)x, o, 64));
+  if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint64_t all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; w++) all += s_w[w];
+    if (all) atomicAdd(reinterpret_cast<unsigned long long*>(sum), (unsigned long long)all);
+  }
+}
 
 // Single-pass exclusive scan of f(i) over i < count, handing (i, prefix,
 // value) to g.  Workgroups take 2048 items each in ticket order (8192 from
@@ -232,7 +249,7 @@ constexpr int kPsum = 16, kPsumStride = 32;  // words of one sum, a cache line a
 template <class F, class G, bool FLAGS, bool HIST, int THREADS>
 __global__ void __launch_bounds__(THREADS) k_scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap,
                                                   uint32_t* ticket, uint64_t* status, uint32_t* total_out,
-                                                  uint32_t* ghist, uint32_t* psum, HostCount host, uint32_t* err) {
+                                                  uint32_t* ghist, uint64_t* psum, HostCount host, uint32_t* err) {
   __shared__ uint32_t s_blk, s_pre;
   __shared__ uint32_t s_h[HIST ? kMaxPasses : 1][256];
   constexpr int kChunkT = THREADS * kItems;
@@ -263,9 +280,10 @@ __global__ void __launch_bounds__(THREADS) k_scan1(F f, G g, const uint32_t* cou
   }
   uint32_t key[FLAGS ? kItems : 1];
   if constexpr (FLAGS) {
-    uint32_t all;
-    block_scan_excl<THREADS / 64>(sum, all);
-    if (t == 0 && all) atomicAdd(&psum[blk % kPsum * kPsumStride], all);
+    sum = 0;
+#pragma unroll
+    for (int k = 0; k < kItems; k++) sum = __builtin_elementwise_add_sat(sum, v[k]);
+    block_add<THREADS / 64>(sum, &psum[blk % kPsum * kPsumStride]);
     sum = 0;
 #pragma unroll
     for (int k = 0; k < kItems; k++) {
@@ -336,7 +354,7 @@ __global__ void __launch_bounds__(THREADS) k_scan1(F f, G g, const uint32_t* cou
 
 template <bool FLAGS, bool HIST, class F, class G>
 void scan1(F f, G g, const uint32_t* count_ptr, uint32_t fixed, uint32_t cap, int64_t bound, uint32_t* ticket,
-           uint64_t* status, uint32_t* total_out, uint32_t* ghist, uint32_t* psum, HostCount host, uint32_t* err, hipStream_t st) {
+           uint64_t* status, uint32_t* total_out, uint32_t* ghist, uint64_t* psum, HostCount host, uint32_t* err, hipStream_t st) {
   auto launch = [&](auto kernel, int threads) {
     const int64_t chunk = (int64_t)threads * kItems;
     const int64_t nb = std::max<int64_t>((bound + chunk - 1) / chunk, 1);  // one workgroup writes a zero total
@@ -760,13 +778,16 @@ __global__ void __launch_bounds__(kBlock) k_rank(const uint32_t* __restrict__ ke
 __global__ void __launch_bounds__(kBlock) k_rects(ViewTable vt, const Rec* __restrict__ rec,
                                                   const uint32_t* __restrict__ dval,
                                                   const uint32_t* __restrict__ place, uint32_t* __restrict__ dsorted,
-                                                  const uint32_t* __restrict__ psum, HostCount host,
+                                                  const uint64_t* __restrict__ psum, HostCount host,
                                                   uint32_t* __restrict__ counters,
                                                   uint32_t* __restrict__ rect0, uint32_t* __restrict__ rect1) {
   const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
   if (blockIdx.x == 0 && threadIdx.x < 64) {
-    const uint32_t s = wave_scan_incl(threadIdx.x < kPsum ? psum[threadIdx.x * kPsumStride] : 0u);
-    if (threadIdx.x == 63) {
+    uint64_t sum = threadIdx.x < kPsum ? psum[threadIdx.x * kPsumStride] : 0u;
+#pragma unroll
+    for (int o = kPsum / 2; o > 0; o >>= 1) sum += (uint64_t)__shfl_xor((unsigned long long)sum, o, 64);
+    if (threadIdx.x == 0) {
+      const uint32_t s = pair_total(sum);
       counters[1] = s;
       counters[7] = 0u;
       publish(host, s);
@@ -802,8 +823,10 @@ struct CountVal {
 };
 struct StoreRange {
   uint2* ranges;
+  uint32_t pcap;
   __device__ void operator()(int64_t i, uint32_t pre, uint32_t n) const {
-    ranges[i] = n ? make_uint2(pre, pre + n) : make_uint2(0u, 0u);
+    const PairRange r = pair_range(pre, n, pcap);
+    ranges[i] = make_uint2(r.first, r.end);
   }
 };
 // The item offset of each depth-sorted entry, and for every emission block
@@ -1517,7 +1540,7 @@ void launch_bin_count(SortBuffers& b, const ViewTable& vt, bool prepped, hipStre
                        (const uint32_t*)nullptr, (const uint32_t*)nullptr, 0u, (uint32_t*)nullptr, (int64_t)0, 0u);
   }
   // compaction of the binned entries with their depth keys, and for the passes the keys' digit histograms
-  uint32_t* psum = rs.tickets + 256;
+  uint64_t* psum = reinterpret_cast<uint64_t*>(rs.tickets + 256);
   const TileCount tc{b.tiles};
   const CompactDepth cd{b.depth, b.dkey[0], b.dval[0]};
   uint32_t* ticket = rs.tickets + kMaxPasses;
@@ -1539,13 +1562,13 @@ void launch_bin_count(SortBuffers& b, const ViewTable& vt, bool prepped, hipStre
   }
   hipLaunchKernelGGL(k_rects, dim3(std::max(1u, (E + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, vt, b.rec,
                      (const uint32_t*)b.dval[place ? 0 : b.dsorted], (const uint32_t*)place, b.dval[1],
-                     (const uint32_t*)psum, b.host_pairs, b.counters, b.dkey[0], b.dkey[1]);
+                     (const uint64_t*)psum, b.host_pairs, b.counters, b.dkey[0], b.dkey[1]);
   // item offsets in depth order
   if (!tests_entries(b))
     scan1<false, false>(PatchCount{b.dkey[0], b.dkey[1]},
                  StoreOffset{b.poff, b.blk_start, b.nblk_start, (int64_t)kBlock * sort_items(b.pcap)},
                  &b.counters[0], 0u, E, b.E, rs.tickets + kMaxPasses + 1, rs.scan_status + rs.nscan, &b.counters[7],
-                 (uint32_t*)nullptr, (uint32_t*)nullptr, b.host_items, &b.counters[3], st);
+                 (uint32_t*)nullptr, (uint64_t*)nullptr, b.host_items, &b.counters[3], st);
 }
 
 void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t items_hint, bool regrown, hipStream_t st) {
@@ -1576,9 +1599,9 @@ void launch_bin_emit(SortBuffers& b, const ViewTable& vt, int64_t items_hint, bo
     hipLaunchKernelGGL(k_list_scan, dim3((unsigned)b.total_patches + gz), dim3(kScanThreads), 0, st, vt,
                        (const uint2*)b.ranges, (const uint32_t*)b.counters, cap, list_chunk, table, b.tile_order,
                        b.order_state, (const uint32_t*)b.tiles, b.E, b.g2d);
-    scan1<false, false>(CountVal{b.tile_order}, StoreRange{b.ranges}, nullptr, T, T, T, rs.tickets,
+    scan1<false, false>(CountVal{b.tile_order}, StoreRange{b.ranges, cap}, nullptr, T, T, T, rs.tickets,
                  reinterpret_cast<uint64_t*>(rs.tickets + kGhStride), (uint32_t*)nullptr, (uint32_t*)nullptr,
-                 (uint32_t*)nullptr, HostCount{}, &b.counters[3], st);
+                 (uint64_t*)nullptr, HostCount{}, &b.counters[3], st);
   };
   const unsigned ow = order_wgs(T);
   int cur = 0;
@@ -1656,7 +1679,7 @@ void launch_count_scan(const uint32_t* cnt, int64_t n, uint32_t* off, uint32_t* 
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, state, words);
   const uint32_t N = (uint32_t)n;
   scan1<false, false>(CountVal{cnt}, CountOffset{off}, nullptr, N, N, n, state, reinterpret_cast<uint64_t*>(state + 2), total,
-               (uint32_t*)nullptr, (uint32_t*)nullptr, host, err, st);
+               (uint32_t*)nullptr, (uint64_t*)nullptr, host, err, st);
 }
 
 int64_t sort_state_words(int64_t bound, bool pairs) {
