@@ -81,8 +81,9 @@ typedef struct {
                           0: automatic (128 below 16,384 tiles in the call's
                           views, 256 from there on; never above the chunk) */
   int64_t pair_capacity; /* 0: grow the (tile, Gaussian) pair buffers on demand
-                            (sixdgs_forward then waits once on the stream to
-                            read the pair count); > 0: fixed capacity, no host
+                            (sixdgs_forward then waits until the stream has
+                            come to the pair count, reads it, and enqueues the
+                            rest); > 0: fixed capacity, no host
                             waits (capturable), overflow reported as
                             SIXDGS_ERR_CAPACITY by sixdgs_check().  At most
                             2^30 - 1 pairs either way (CAPACITY beyond). */
@@ -262,8 +263,8 @@ typedef struct {
  * spatial means are mu_p + R (S * z_k) and whose spatial Cholesky block L_p
  * is divided by 1.6, so S shrinks by 1.6 and R is kept), from stats (device
  * [2][n]: the summed screen-space gradient norm and the visible-view count
- * that sixdgs_backward accumulates into `densify`).  Waits for the stream and
- * writes the number of output Gaussians to *n_out (host).  The plan stays in
+ * that sixdgs_backward accumulates into `densify`).  Waits for the stream (it
+ * is idle on return) and writes the number of output Gaussians to *n_out (host).  The plan stays in
  * ctx for the next sixdgs_densify_apply with the same params and n. */
 sixdgs_status sixdgs_densify_plan(sixdgs_ctx* ctx, const float* params, int64_t n, const float* stats,
                                   const sixdgs_density_settings* settings, int64_t* n_out, void* stream);

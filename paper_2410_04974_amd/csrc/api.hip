@@ -1102,7 +1102,9 @@ static sixdgs_status densify_plan_body(sixdgs_ctx* c, const float* params, int64
   launch_count_scan(c->dens_cnt.p, n, c->dens_off.p, c->counters.p + 5, host, c->dens_state.p,
                     c->counters.p + 3, st);
   int64_t total = 0;
-  if (!wait_count(host, st, total)) return fail(c, SIXDGS_ERR_HIP, "density plan read-back failed");
+  // the count comes before the last offsets: the call also waits for those
+  if (!wait_count(host, st, total) || hipStreamSynchronize(st) != hipSuccess)
+    return fail(c, SIXDGS_ERR_HIP, "density plan read-back failed");
   c->dens_params = params;
   c->dens_n = n;
   c->dens_total = total;
