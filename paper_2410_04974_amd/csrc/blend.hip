@@ -707,6 +707,30 @@ __device__ __forceinline__ void bwd_group(BwdWave& W, BwdGauss& G, float col, ui
   if (FORM == kFree || pos0 < W.qlast[3]) bwd_steps<3, FORM>(W, G, col);
 }
 
+__device__ __forceinline__ bool finite(float x) { return fabsf(x) < __builtin_huge_valf(); }
+
+// The pixels of the block (first at x0, y0) whose dL/dC is not finite, by the
+// lane that holds them, against staged Gaussian s at list position pos: where
+// such a pixel takes it, its channels that are not finite go to the Gaussian's
+// colour sums, and its other sums become undefined.  Every lane calls; `in`:
+// whether it has a Gaussian.
+__device__ __forceinline__ void not_finite(const Staged& s, bool in, uint32_t pos, float* sums, uint64_t odd,
+                                           uint32_t lastcmp, const ViewDesc& vd, int x0, int y0) {
+  for (; odd; odd &= odd - 1) {
+    const int q = __ffsll((unsigned long long)odd) - 1;
+    const int x = x0 + (q & 7), y = y0 + 4 * ((q >> 3) & 1) + (q >> 4);
+    const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)lastcmp, q);
+    const float p = log2_alpha(s.a, s.b, ((float)x + 0.5f) - s.a.x, ((float)y + 0.5f) - s.a.y);
+    if (!(in && p >= kLog2AlphaMin && pos < last)) continue;
+    for (int c = 0; c < 3; c++) {
+      const float d = vd.dimg[((int64_t)c * vd.H + y) * vd.W + x];
+      if (!finite(d)) atomicAdd(sums + 6 + c, d);
+    }
+    if (exp2_fast(p) <= kAlphaMax)
+      for (int k = 0; k < 6; k++) atomicAdd(sums + k, __builtin_nanf(""));
+  }
+}
+
 // One work item = one chunk of `chunk` list positions of one tile, walked
 // back to front from the state the forward saved where the next chunk begins
 // (or from the pixel's final state for the tile's last chunk).
@@ -770,6 +794,13 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
     dC1 = vd.dimg[HW + pix];
     dC2 = vd.dimg[2 * HW + pix];
   }
+  // An infinite or undefined dL/dC would outlive the products with 0 by which
+  // the walk leaves out Gaussians and pixels: such a channel is walked as 0, and
+  // the Gaussians that its pixel takes get it afterwards (not_finite).
+  const uint64_t odd = __ballot(!(finite(dC0) && finite(dC1) && finite(dC2)));
+  dC0 = finite(dC0) ? dC0 : 0.f;
+  dC1 = finite(dC1) ? dC1 : 0.f;
+  dC2 = finite(dC2) ? dC2 : 0.f;
   // dL/dC passes through the (not yet used) staging records into the operand
   // of dL/dC . c
   static_assert(sizeof(L.rec) >= sizeof(float4) * kBlock, "dL/dC fits the staged records");
@@ -885,6 +916,12 @@ __global__ void __launch_bounds__(kBlock, MAXB <= 128 ? 5 : 6)
         if (row == 0) atomicAdd(to + 8, k2);
       }
     }
+    if (odd)
+      for (uint32_t i0 = 0; i0 < wn; i0 += 64) {  // (uniform)
+        const uint32_t i = i0 + l, slot = L.list[wv][min(i, wn - 1)];
+        not_finite(L.rec[slot], i < wn, posb + slot, s_g + slot * kG2D, odd, W.lastcmp, vd,
+                   tx * TW + TileMap<TW>::bx(wv), ty * TileMap<TW>::TH + TileMap<TW>::by(wv));
+      }
     __syncthreads();
     // one set of global atomics per (chunk, Gaussian).  Each staged
     // Gaussian's thread turns its column of sums into the nine components in
