@@ -297,7 +297,7 @@ bool ensure_scratch(sixdgs_ctx* c, int64_t E, int64_t pcap) {
   const int64_t e1 = std::max<int64_t>(E, 1);
   const int64_t p1 = std::max<int64_t>(pcap, 1);
   return c->rstate.ensure(sort_state_words(e1, false) + sort_state_words(p1, true) +
-                          list_state_words(e1, c->vt.total_tiles, c->vt.total_patches)) &&
+                          list_state_words(e1, c->vt.total_tiles, c->vt.total_patches, p1)) &&
          c->blk_start.ensure(sort_block_starts(p1));
 }
 

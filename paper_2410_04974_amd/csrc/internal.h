@@ -210,7 +210,7 @@ struct SortBuffers {
 };
 // Scratch sizes (32-bit words) of the integer stage for a bound on the items.
 int64_t sort_state_words(int64_t bound, bool pairs);
-int64_t list_state_words(int64_t E, int64_t total_tiles, int64_t total_patches);
+int64_t list_state_words(int64_t E, int64_t total_tiles, int64_t total_patches, int64_t pcap);
 int64_t sort_block_starts(int64_t pcap);
 int64_t order_state_words();
 // Whether items are sorted (else there are none and counters[7] is 0).

@@ -1686,13 +1686,15 @@ int64_t sort_state_words(int64_t bound, bool pairs) {
   // the pair state sized for the smaller blocks, whichever sort_items picks
   return radix_state(nullptr, bound, kRItemsSmall, !pairs).words();
 }
-// (the rows of sorted items take the place of the passes' tables, which have
-// twice as many words)
-int64_t list_state_words(int64_t E, int64_t total_tiles, int64_t total_patches) {
+// The table's rows take the place of the passes' tables: those of sorted items
+// (besides one a patch) are half as many words, those of tested entries may be
+// more (then there are no passes).
+int64_t list_state_words(int64_t E, int64_t total_tiles, int64_t total_patches, int64_t pcap) {
+  const int64_t tables = (int64_t)kMaxPasses * 256 * radix_blocks(pcap, kRItemsSmall);
   const int64_t rows = test_entries(E, total_patches)
                            ? total_patches * ((E + entry_chunk(E, total_patches) - 1) / entry_chunk(E, total_patches))
                            : 0;
-  return tile_scan_words(total_tiles) + 4 + 64 * (rows + total_patches + 2);
+  return tile_scan_words(total_tiles) + 4 + 64 * (total_patches + 2) + std::max<int64_t>(64 * rows - tables, 0);
 }
 int64_t sort_block_starts(int64_t pcap) { return radix_blocks(pcap, kRItemsSmall) + 1; }
 int64_t order_state_words() { return kOrderStateWords; }
