@@ -542,7 +542,10 @@ std::string debug_check_binning(sixdgs_ctx* c, const float* depth_dev, bool item
     if ((int64_t)e >= E) return "pair " + std::to_string(i) + ": entry id " + std::to_string(e) + " >= " + std::to_string(E);
     const ViewDesc& vd = c->vt.v[e / c->vt.n];
     const Rec& r = rec[e];
-    auto cell = [](float x, int shift) { return (int)std::fmin(std::fmax(std::floor(x / (float)(1 << shift)), -2e9f), 2e9f); };
+    // (a caller's NaN is in cell 0, as the device converts it)
+    auto cell = [](float x, int shift) {
+      return std::isnan(x) ? 0 : (int)std::fmin(std::fmax(std::floor(x / (float)(1 << shift)), -2e9f), 2e9f);
+    };
     const int sx = c->vt.tile_shift_x, sy = c->vt.tile_shift_y;
     const int local = (int)t - vd.tile_base, x = local % vd.ntx, y = local / vd.ntx;
     if (local < 0 || y >= vd.nty || x < cell(r.a.x - r.b.z, sx) || x > cell(r.a.x + r.b.z, sx) ||
