@@ -791,7 +791,7 @@ sixdgs_status forward_impl(sixdgs_ctx* c, const float* params, const float* cach
   }
   {
     Timer t(c, SIXDGS_K_BLEND_FWD, st);
-    launch_blend_fwd(vt, ds, c->rec.p, c->ranges.p, c->sb.pval[c->sb.psorted], bs, c->fwd_batch, !inference, st);
+    launch_blend_fwd(vt, ds, c->rec.p, c->ranges.p, c->sb.pval[c->sb.psorted], bs, !inference, st);
   }
   if (with_l1) launch_l1_final(c->l1_partial.p, vt.total_tiles, bs.l1_inv, loss, c->l1_partial.p + vt.total_tiles, st);
   if (inference) return check_launch(c, "blend forward");

@@ -983,7 +983,7 @@ void launch_fwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const
 }  // namespace
 
 void launch_blend_fwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges,
-                      const uint32_t* pval, BlendState bs, int batch, bool save, hipStream_t st) {
+                      const uint32_t* pval, BlendState bs, bool save, hipStream_t st) {
   if (vt.total_tiles <= 0) return;
   switch (vt.tile_w) {
     case 8: launch_fwd<8>(vt, s, rec, ranges, pval, bs, save, st); break;

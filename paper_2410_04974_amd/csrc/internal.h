@@ -265,7 +265,7 @@ struct BlendState {
 };
 // save = false: the image only, none of the state a backward needs
 void launch_blend_fwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges,
-                      const uint32_t* pval, BlendState bs, int batch, bool save, hipStream_t st);
+                      const uint32_t* pval, BlendState bs, bool save, hipStream_t st);
 // `grid` bounds the number of backward work items (pairs / chunk + tiles).
 void launch_blend_bwd(const ViewTable& vt, const DevSettings& s, const Rec* rec, const uint2* ranges,
                       const uint32_t* pval, BlendState bs, float* g2d, int batch, int64_t grid, hipStream_t st);
