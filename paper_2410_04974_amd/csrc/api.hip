@@ -183,7 +183,8 @@ sixdgs_status fail(sixdgs_ctx* c, sixdgs_status st, const std::string& msg) {
 
 // counters: [0] binned entries, [1] pairs, [2] pair overflow flag, [3] look-back
 // timeout flag, [4] backward work items, [5] density-control outputs, [6] the
-// fused backward + Adam's finished workgroups (zero between launches)
+// fused backward + Adam's finished workgroups (zero between launches), [7] the
+// integer stage's sorted items
 constexpr int kCounters = 8;
 constexpr int kHostWords = 2;
 

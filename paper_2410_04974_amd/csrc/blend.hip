@@ -737,13 +737,13 @@ __device__ __forceinline__ void not_finite(const Staged& s, bool in, uint32_t po
 //
 // Bound by the vector instructions it issues.  With a pixel per lane for the
 // whole walk, a Gaussian cost 65 of them, 24 for the sums of its nine values
-// over the wavefront; here a group of 16 takes 31 a step and Gaussian without
+// over the wavefront; here a group of 16 takes 30 a step and Gaussian without
 // a reduction (the product dL/dC . c is four f32 matrix products a group, which
 // share the vector units' rate but replace 48 instructions by 32 issue slots;
 // the colour sums are cheaper as vector instructions: 3465 against 3780 us
 // with matrix products on sixteen uneven views of 500k Gaussians).  Vector
-// instructions there 2.81 -> 1.6 G, time 4796 -> 3410 us; one 800x800 view of
-// 300k Gaussians 228 -> 169 us; eight 1080p views of 1M: step 8.50 -> 7.07 ms.
+// instructions there 2.81 -> 1.6 G, time 4803 -> 3313 us; one 800x800 view of
+// 300k Gaussians 224 -> 164 us; eight 1080p views of 1M 4950 -> 3371.
 // Registers: 95 hold the walk without spills, five wavefronts per SIMD; six
 // (80, a few spilled outside the steps) are 2% faster where the launch has
 // many long lists (MAXB = 256) and 8% slower on one 403x301 view.

@@ -132,8 +132,8 @@ __device__ __forceinline__ void adam_update(float& p, float g, float& m, float& 
 // preprocess.hip
 // cache: nullptr, or the inference cache of params (then the slice's
 // direction-independent part is read instead of computed)
-// The integer stage's preparation -- state words to zero and the tile ranges
-// set to (UINT_MAX, 0) -- done by the threads of the launch before the stage
+// The integer stage's preparation -- state words to zero and the ranges, where
+// the patches' ranges of the items go first, set to (UINT_MAX, 0) -- done by the threads of the launch before the stage
 // (thread i takes word i of every region), which saves the stage a launch.
 struct BinPrep {
   uint32_t* p[4];
@@ -146,7 +146,7 @@ __device__ __forceinline__ void bin_prep_at(const BinPrep& bp, int64_t i) {
 #pragma unroll
   for (int k = 0; k < 4; k++)
     if (bp.p[k] && i < bp.n[k]) bp.p[k][i] = 0u;
-  if (bp.ranges && i < bp.nranges) bp.ranges[i] = make_uint2(0xFFFFFFFFu, 0u);  // merged by min / max
+  if (bp.ranges && i < bp.nranges) bp.ranges[i] = make_uint2(0xFFFFFFFFu, 0u);  // a patch without items
 }
 // With bp, the launch also does the integer stage's preparation (then the
 // return value is true and launch_bin_count is told so).
@@ -296,7 +296,7 @@ void launch_l1(int nimg, const float* const* img, const float* const* tgt, const
                float* const* dimg, float* partial, int64_t partial_cap, float* loss, hipStream_t st);
 int64_t l1_partial_count(int nimg, const int64_t* numel);
 // (1 - lam) L1 + lam (1 - SSIM) over nimg [3][H][W] views: maps holds
-// 9 floats per pixel of every view, partial 2 floats per 16x16 tile and channel.
+// 9 floats per pixel of every view, partial 2 floats per 32x16 tile and channel.
 int64_t ssim_blocks(int H, int W);
 void launch_l1_dssim(int nimg, const float* const* img, const float* const* tgt, const int32_t* H, const int32_t* W,
                      float lam, float* const* dimg, float* maps, float* partial, float* loss, hipStream_t st);

@@ -60,11 +60,11 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t& total)
 
 // ------------------------------------------------------------ radix sort
 // The depth order's passes (the item sort's are further below): one kernel
-// per pass, where each workgroup takes the next 4096 items in ticket
-// order, ranks them stably by digit in LDS, and finds where its items of each
-// digit go by looking back over the per-digit counts that earlier workgroups
-// publish (a status word per digit: aggregate of that workgroup alone, or
-// inclusive prefix through it).  The global digit offsets come from a
+// per pass, where each workgroup takes the next 2,048 items (4,096 from
+// kLargeSort entries on) in ticket order, ranks them stably by digit in LDS, and
+// finds where its items of each digit go by looking back over the per-digit
+// counts that earlier workgroups publish (a status word per digit: aggregate of
+// that workgroup alone, or inclusive prefix through it).  The global digit offsets come from a
 // histogram of every pass taken before the first pass, so each pass reads and
 // writes the data once.  Tickets make a workgroup wait only on workgroups that
 // are already running; the wait is bounded and reports a timeout in the error
@@ -74,9 +74,13 @@ constexpr int kRItemsSmall = 8;           // short sorts: 2048 items per workgro
 constexpr int64_t kLargeSort = 1 << 20;    // from this many entries the depth sort uses kRItems
 constexpr int64_t kLargePairs = 1 << 27;   // from this pair capacity on the items' sort uses kRItems
 // Items per thread of the item sort's workgroups (and items per emission
-// block: kBlock times this); a dozen pairs are an item.  Emission, counts, scans
-// and scatters with 8 and with 16: 144M pairs (16 views of 500k) 215 and 185 us,
-// 49M pairs (8 1080p views of 1M) 70 and 78.
+// block: kBlock times this); a dozen pairs are an item.  By the capacity, which
+// sizes the fixed mode's grids whatever the scene: larger blocks then leave half
+// as many workgroups to find nothing to do.  The stage with 8 and with 16: one
+// 1600x900 view of 500k (17M pairs) at a capacity of 26M 185 and 197 us, 134M
+// 197 and 195, 537M 277 and 223; 8 1080p views of 1M (49M) at 74M 444 and 456,
+// 134M 464 and 455; 8 uneven views of 500k (74M) at 111M 554 and 563; 16 (146M)
+// at 219M 988 and 953.
 inline int sort_items(int64_t pcap) { return pcap >= kLargePairs ? kRItems : kRItemsSmall; }
 constexpr uint32_t kStAgg = 1u << 30;
 constexpr uint32_t kStIncl = 2u << 30;
@@ -390,7 +394,7 @@ __global__ void __launch_bounds__(kBlock) k_stage_prep(RadixState rs, int64_t ze
 #pragma unroll
   for (int k = 0; k < 4; k++)
     if (z.p[k] && i < z.n[k]) z.p[k][i] = 0u;
-  if (ranges && i < nranges) ranges[i] = make_uint2(0xFFFFFFFFu, 0u);  // merged by min / max
+  if (ranges && i < nranges) ranges[i] = make_uint2(0xFFFFFFFFu, 0u);  // a patch without items
   if (blk_start && i < (int64_t)counters[0] && counters[1] <= pcap) {
     const uint32_t o = poff[i];
     const uint32_t end = i + 1 < (int64_t)counters[0] ? poff[i + 1] : *total;
@@ -1049,10 +1053,10 @@ __device__ __forceinline__ void order_tiles(const uint2* __restrict__ ranges, ui
 // the second kernel's lanes then know where their entries go, in each tile a
 // dozen neighbours or so at a time.  Radix sorting the pairs (8 bytes) by tile
 // moved each five times, 124 vector instructions per 64 and pass, and bound the
-// stage by memory: 16 views of 500k Gaussians, 144M pairs, 3,350 us for the
-// whole stage then and 1,035 now (283 of them the writes, 2.0 TB/s: runs of
-// 50 bytes); one 1408x1408 view of 175k, 4.9M pairs, 195 and 110; one 800x800
-// view of 300k, 3.4M pairs, 164 and 120.
+// stage by memory: 16 views of 500k Gaussians, 144M pairs, 3,235 us for the
+// whole stage then and 953 now (283 of them the writes, 2.0 TB/s: runs of
+// 50 bytes); one 1408x1408 view of 175k, 4.9M pairs, 181 and 106; one 800x800
+// view of 300k, 3.4M pairs, 158 and 113.
 __device__ __forceinline__ uint32_t readlane(uint32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
 // lane q of (lo, hi) = m (a vector instruction may read a scalar register that
 // another wrote two wait states later)
