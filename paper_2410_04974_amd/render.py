@@ -141,7 +141,7 @@ class Trainer:
     def step(self, cams, targets, densify=None, fused=True):
         """Render, L1 loss, backward, Adam.  fused=True applies Adam at the end
         of the preprocess backward (the gradient rows stay in LDS and never
-        reach memory: 649 against 677 us per step on the 300k-Gaussian
+        reach memory: 525 against 567 us per step on the 300k-Gaussian
         800x800 step on MI355X); fused=False writes the gradient to self.grad
         and runs the streaming Adam kernel.  Both read and advance the step
         count on the device, so a step can be captured in a graph."""
